@@ -87,8 +87,16 @@ def flops(B, H, N, d, causal, dv=None):
 
 
 def kernel_source_sha256() -> str:
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    """Hash of the kernel sources: KERNEL_SOURCE, then the other .hip and .h
+    files of its folder in the package, by name."""
+    csrc = os.path.join(ROOT, "paper_2506_12355_amd", "csrc")
+    rest = sorted(n for n in os.listdir(csrc)
+                  if n.endswith((".hip", ".h")) and n != "attn_fwd_gfx950.hip")
+    h = hashlib.sha256()
+    for path in [KERNEL_SOURCE] + [os.path.join(csrc, n) for n in rest]:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def committed_traffic(workload: str = si.BENCH_WORKLOAD):
