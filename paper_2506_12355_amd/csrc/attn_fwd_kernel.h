@@ -162,8 +162,10 @@ struct KParams {
   int Hkv;          // key/value heads
   int group;        // H / Hkv: query heads per key/value head
   int nq;           // query blocks per head
-  int wg_per_head;  // workgroups per head: nq, or ceil(nq / 2) pairs when causal
-  int total;        // wg_per_head * B * H workgroups
+  int paired;       // causal: a tile is a pair of query blocks (else one)
+  int down;         // causal, not paired: tiles per XCD that count query blocks down
+  int wg_per_head;  // tiles per head: nq, or ceil(nq / 2) when paired
+  int total;        // wg_per_head * B * H tiles
   float c;     // |scale| * log2 e (FP8: |scale * q_scale * k_scale| * log2 e)
   float vscale;  // factor of O: 1, or the FP8 value scale
   int qmode;
@@ -453,6 +455,11 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
   // A tile is one (batch*head, query block), or, causal, the pair (nq-1-i, i)
   // of query blocks (query block qb costs qb + 1 units of key blocks, so every
   // pair costs the same and the grid has no long tail; the longer runs first).
+  // Where all causal query blocks run at once they stay single: the longest
+  // alone is shorter than a pair, and one's prologue runs beside another's
+  // blocks.  The first p.down tiles of an XCD count a head's query blocks down
+  // and the others up, so that the two blocks a CU may hold (one from each half
+  // of the XCD's tiles) complement each other.
   // Workgroup w walks tiles w, w + grid, ....  16-bit inputs: the grid holds as
   // many workgroups as the CUs run at once (a multiple of 8), so the launch gap
   // and set-up of a new workgroup are paid once per CU, not per tile.  FP8
@@ -468,8 +475,8 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
     qb = id - bh * p.wg_per_head;
     if (CAUSAL) {
       const int other = p.nq - 1 - qb;
-      qb2 = qb != other ? qb : -1;
-      qb = other;
+      if (p.paired) qb2 = qb != other ? qb : -1;
+      if (p.paired || tile / kXcds < p.down) qb = other;
     }
   };
 
@@ -1207,8 +1214,16 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
 
 // ---- host side: kernel arguments and the launch of one instance ----
 
-// The kernel's arguments for query blocks of bm rows.
-inline KParams make_params(const AttnArgs& a, int bm) {
+// The kernel's arguments for query blocks of bm rows; `resident`: workgroups the
+// device's CUs hold at once.
+//
+// Causal query blocks stay single (see attn_fwd_body) when each has a CU to
+// itself, or, up to N = 2048, when all are resident.  Measured against pairs
+// (d = 128 bf16, B = 1, us): N = 250 H = 8 15.2 -> 9.4, N = 512 H = 64
+// 19.1 -> 13.5, N = 2048 H = 16 37.4 -> 33.8; two workgroups per CU: N = 1000
+// H = 64 27.3 -> 25.4, N = 2048 H = 32 42.0 -> 42.1, N = 4096 H = 16
+// 78.3 -> 78.8, N = 8192 H = 8 142.6 -> 148.0.
+inline KParams make_params(const AttnArgs& a, int bm, int cus, int resident) {
   KParams kp;
   kp.q = static_cast<const uint8_t*>(a.q);
   kp.k = static_cast<const uint8_t*>(a.k);
@@ -1220,8 +1235,12 @@ inline KParams make_params(const AttnArgs& a, int bm) {
   kp.Hkv = a.Hkv;
   kp.group = a.H / a.Hkv;
   kp.nq = (a.N + bm - 1) / bm;
-  kp.wg_per_head = a.causal ? (kp.nq + 1) / 2 : kp.nq;
+  const long long blocks = (long long)kp.nq * a.B * a.H;
+  kp.paired = a.causal && blocks > cus && (a.N > 2048 || blocks > resident);
+  kp.wg_per_head = kp.paired ? (kp.nq + 1) / 2 : kp.nq;
   kp.total = kp.wg_per_head * a.B * a.H;
+  // half of an XCD's tiles when whole heads fall in each half, else all
+  kp.down = kp.total % (2 * kXcds * kp.nq) == 0 ? kp.total / (2 * kXcds) : kp.total;
   kp.c = a.c;
   kp.vscale = a.vscale;
   kp.qmode = a.qmode;
@@ -1229,37 +1248,39 @@ inline KParams make_params(const AttnArgs& a, int bm) {
   return kp;
 }
 
-// Launch KERN over kp's tiles: per_cu workgroups on each CU walk them
-// (persistent), or one workgroup per tile when per_cu is 0.
+// The current device and its CU count.
+struct Device {
+  int id = 0, cus = 0;
+};
+inline hipError_t current_device(Device* d) {
+  const hipError_t e = hipGetDevice(&d->id);
+  if (e != hipSuccess) return e;
+  return hipDeviceGetAttribute(&d->cus, hipDeviceAttributeMultiprocessorCount, d->id);
+}
+
+// Launch KERN over the tiles of query blocks of bm rows: per_cu workgroups on
+// each CU walk them (persistent), or one workgroup per tile.
 template <void (*KERN)(KParams)>
-hipError_t launch_tiles(const KParams& kp, int threads, size_t lds, int per_cu,
-                        hipStream_t stream) {
+hipError_t launch_tiles(const AttnArgs& a, const Device& dev, int bm, int threads, size_t lds,
+                        int per_cu, bool persistent, hipStream_t stream) {
   // The dynamic LDS limit is a per-device attribute of the kernel: raise it
   // once on each device this instance runs on (bit d of `ready`: device d;
   // devices past 63 set it on every call).  Concurrent first calls may both
   // set it, which is harmless.
   static std::atomic<uint64_t> ready{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+  const uint64_t bit = dev.id < 64 ? 1ull << dev.id : 0;
   if (!bit || !(ready.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ready.fetch_or(bit, std::memory_order_release);
   }
   // Persistent workgroups: as many as the CUs hold at once, rounded down to a
   // multiple of the XCD count so that tile t still runs on XCD t % 8 (the
   // dispatcher deals workgroup w to XCD w % 8)
-  int grid = kp.total;
-  if (per_cu) {
-    int cus = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const int resident = cus * per_cu / kXcds * kXcds;
-    if (resident >= kXcds && resident < grid) grid = resident;
-  }
+  const int resident = dev.cus * per_cu / kXcds * kXcds;
+  const KParams kp = make_params(a, bm, dev.cus, resident);
+  const int grid = persistent && resident >= kXcds && resident < kp.total ? resident : kp.total;
   hipLaunchKernelGGL(KERN, dim3(grid), dim3(threads), lds, stream, kp);
   return hipGetLastError();
 }
