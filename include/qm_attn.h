@@ -245,6 +245,10 @@ int qm_attn_fwd_fp8_layout(const void* q, const void* k, const void* v, void* o,
  *   rows = 128 or 256: that size wherever it exists ([B][H][N][d] tensors with
  *            head dimension 64 or 128; everything else runs 256).
  *
+ * Calls whose query blocks all fit the device at once (a few heads, N >= 384)
+ * run workgroups of 64 or 128 rows that split the keys between their
+ * wavefronts, whatever this setting is.
+ *
  * Results do not depend on it: every query row takes the same arithmetic in
  * the same order, so outputs are byte-identical either way; only speed
  * changes.  Returns QM_OK, or QM_ERR_TILE for any other value (the setting is

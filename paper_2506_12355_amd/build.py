@@ -14,6 +14,8 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
@@ -23,7 +25,7 @@ LIB_NAME = "libqm_attn.so"
 LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 DEBUG_LIB_PATH = os.path.join(PKG_DIR, "libqm_attn_debug.so")
 
-SOURCES = ["qm_attn.cpp", "attn_fwd_gfx950.hip"]
+SOURCES = ["qm_attn.cpp", "attn_fwd_gfx950.hip", "attn_fwd_split_gfx950.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -47,36 +49,47 @@ def hipcc() -> str:
     return path
 
 
-def build_command(out_path: str = LIB_PATH, debug_sync: bool = False) -> list:
-    return ([hipcc()] + HIPCC_FLAGS + (["-DQM_DEBUG_SYNC"] if debug_sync else [])
-            + ["-I", INCLUDE, "-I", CSRC, "-o", out_path]
-            + [os.path.join(CSRC, s) for s in SOURCES])
+def compile_command(source: str, out_path: str, debug_sync: bool = False) -> list:
+    flags = [f for f in HIPCC_FLAGS if f != "-shared"]
+    return ([hipcc()] + flags + (["-DQM_DEBUG_SYNC"] if debug_sync else [])
+            + ["-I", INCLUDE, "-I", CSRC, "-c", "-o", out_path, os.path.join(CSRC, source)])
+
+
+def link_command(objects: list, out_path: str) -> list:
+    return [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out_path] + objects
+
+
+def _run_all(commands: list, verbose: bool) -> None:
+    """Run the commands, as many at once as there are CPUs to keep busy."""
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        return cmd, subprocess.run(cmd, capture_output=True, text=True)
+
+    failed = []
+    with ThreadPoolExecutor(max_workers=min(len(commands), len(os.sched_getaffinity(0)), 16)) as ex:
+        for cmd, res in ex.map(run, commands):
+            if res.returncode != 0:
+                failed.append(f"{' '.join(cmd)} failed ({res.returncode}):\n{res.stdout}\n{res.stderr}")
+            elif verbose and res.stderr.strip():
+                print(res.stderr, file=sys.stderr)
+    if failed:
+        raise RuntimeError("\n".join(failed))
 
 
 def build(verbose: bool = False) -> str:
     """Compile every source into ``libqm_attn.so`` and ``libqm_attn_debug.so``
-    (two hipcc processes at once; each library atomically replaced)."""
-    jobs = []
-    for path, debug in ((LIB_PATH, False), (DEBUG_LIB_PATH, True)):
-        tmp = path + f".tmp{os.getpid()}"
-        cmd = build_command(tmp, debug_sync=debug)
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        jobs.append((path, tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE,
-                                                 stderr=subprocess.PIPE, text=True)))
-    failed = []
-    for path, tmp, proc in jobs:
-        out, err = proc.communicate()
-        if proc.returncode != 0:
-            if os.path.exists(tmp):
-                os.remove(tmp)
-            failed.append(f"hipcc failed for {path} ({proc.returncode}):\n{out}\n{err}")
-            continue
-        if verbose and err.strip():
-            print(err, file=sys.stderr)
-        os.replace(tmp, path)
-    if failed:
-        raise RuntimeError("\n".join(failed))
+    (sources compiled side by side; each library atomically replaced)."""
+    with tempfile.TemporaryDirectory() as tmp:
+        compiles, links = [], []
+        for path, debug in ((LIB_PATH, False), (DEBUG_LIB_PATH, True)):
+            objects = [os.path.join(tmp, f"{s}.{int(debug)}.o") for s in SOURCES]
+            compiles += [compile_command(s, o, debug) for s, o in zip(SOURCES, objects)]
+            links.append(link_command(objects, path + f".tmp{os.getpid()}"))
+        _run_all(compiles, verbose)
+        _run_all(links, verbose)
+    for path in (LIB_PATH, DEBUG_LIB_PATH):
+        os.replace(path + f".tmp{os.getpid()}", path)
     return LIB_PATH
 
 

@@ -46,6 +46,8 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t stream) {
   Device dev;
   const hipError_t e = current_device(&dev);
   if (e != hipSuccess) return e;
+  const int groups = key_groups(a, dev.cus);
+  if (groups > 1) return launch_attn_fwd_split(a, groups, stream);
   // Workgroup size.  Eight waves (256 query rows, one workgroup per CU) keep
   // K/V tiles in LDS for the most rows; four waves (128 rows, two or three
   // workgroups per CU) let one workgroup's prologue and epilogue run beside

@@ -34,9 +34,17 @@ struct AttnArgs {
   int tile_rows;  // query rows per workgroup: 0 = chosen from the shape, 128 or 256
 };
 
-// Enqueues the kernel instance for (d, dv, dtype, causal, workgroup size).
-// Arguments have been
+// Enqueues the kernel instance for (d, dv, dtype, causal, workgroup size, key
+// groups).  Arguments have been
 // validated by the caller.  Returns the HIP launch status.
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t stream);
+
+// Key groups of a workgroup (1, 2 or 4) that a call runs with on a device of
+// `cus` CUs.  A function of the shape, type and mask alone: not of tile_rows or
+// layout, on which results do not depend.
+int key_groups(const AttnArgs& a, int cus);
+
+// Enqueues the instance with `groups` (2 or 4) key groups.
+hipError_t launch_attn_fwd_split(const AttnArgs& a, int groups, hipStream_t stream);
 
 }  // namespace qm

@@ -1,14 +1,19 @@
 """Grids too small to fill the device: causal query blocks run one per
 workgroup instead of in pairs, in an order that depends on how the heads fall on
-the XCDs.  Shapes on both sides of each rule, head counts that do and do not
-divide over the XCDs, ragged lengths; every output against the oracle."""
+the XCDs, and the smallest grids split their keys over two or four groups of a
+workgroup's wavefronts.  Shapes on both sides of each rule, head counts that do
+and do not divide over the XCDs, ragged lengths; every output against the
+oracle."""
 from __future__ import annotations
 
+import math
+
+import numpy as np
 import pytest
 
 import seeded_inputs as si
 from oracle import attention_fp64
-from tests.gpu_util import check_close, to_device, to_host64
+from tests.gpu_util import check_close, half_ulp, to_device, to_host64
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +42,76 @@ def test_causal_small_grid_matches_oracle(qa, B, H, Hkv, N, d, dtype):
     o, lse = qa.fwd(tq, tk, tv, causal=True)
     Or, lr = attention_fp64(q, k, v, si.default_scale(d), True, dtype)
     check_close(to_host64(o), to_host64(lse), Or, lr, dtype, f"small grid {B}x{H}x{N}")
+
+
+# (B, H, Hkv, N, d, dtype, causal, scale multiplier): the lengths on both sides of
+# the rules for two and four key groups on 256 CUs, one block past a whole number of
+# group steps, query blocks in pairs, a negative and a negligible scale
+SPLIT = [
+    (1, 2, 2, 384, 64, "f16", False, 1.0), (1, 2, 2, 383, 64, "f16", False, 1.0),
+    (1, 6, 2, 385, 64, "bf16", True, 1.0), (3, 5, 5, 1001, 64, "bf16", True, 1.0),
+    (1, 4, 1, 4100, 64, "f16", True, 1.0), (1, 7, 7, 4223, 64, "bf16", True, 1.0),
+    (1, 30, 10, 1000, 64, "f16", False, -1.0), (2, 16, 16, 768, 64, "bf16", True, 0.0),
+    (1, 3, 3, 1536, 128, "bf16", False, 1.0), (1, 3, 3, 1535, 128, "bf16", False, 1.0),
+    (1, 5, 5, 1600, 128, "f16", True, 1.0), (2, 3, 1, 1793, 128, "bf16", True, -1.0),
+    (1, 12, 4, 4097, 128, "f16", True, 1.0), (1, 2, 2, 2111, 128, "bf16", False, 0.0),
+]
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d,dtype,causal,mult", SPLIT)
+def test_key_groups_match_oracle_in_both_layouts(qa, B, H, Hkv, N, d, dtype, causal, mult):
+    import torch
+    print(f"case key groups {B}x{H}/{Hkv}x{N}x{d} {dtype} causal={causal} scale x{mult}", flush=True)
+    q, k, v = si.make_qkv(B, H, N, d, dtype, seed=410 + N + H, Hkv=Hkv)
+    scale = si.default_scale(d) * mult
+    tq, tk, tv = (to_device(x, dtype) for x in (q, k, v))
+    o, lse = qa.fwd(tq, tk, tv, causal=causal, scale=scale)
+    Or, lr = attention_fp64(q, k, v, scale, causal, dtype)
+    check_close(to_host64(o), to_host64(lse), Or, lr, dtype, f"key groups {B}x{H}x{N}x{d}")
+    bn = [t.transpose(1, 2).contiguous() for t in (tq, tk, tv)]
+    o2, lse2 = qa.fwd(*bn, causal=causal, scale=scale, layout="bnhd")
+    assert torch.equal(o2.transpose(1, 2).contiguous().view(torch.int16), o.view(torch.int16))
+    assert torch.equal(lse2.view(torch.int32), lse.view(torch.int32))
+
+
+@pytest.mark.parametrize("B,H,Hkv,N", [(1, 3, 3, 384), (1, 4, 2, 1000), (2, 8, 8, 1000), (1, 5, 1, 4161)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_fp8_key_groups_exact_weights(qa, B, H, Hkv, N, causal):
+    """Weights that are exact in E4M3, so only fp32 sums and the bf16 store round:
+    each of up to N + 128 sums moves a row by 2^-24 of sum P|v| twice over."""
+    import torch
+    print(f"case FP8 key groups {B}x{H}/{Hkv}x{N} causal={causal}", flush=True)
+    codes8 = si.make_qkv_fp8_dyadic(B, H, N, 128, seed=510 + N, v_binade=True, Hkv=Hkv)
+    codes = [torch.from_numpy(x).cuda().view(torch.float8_e4m3fn) for x in codes8]
+    scales = (0.5, 2.0, 0.0123)
+    o, lse = qa.fwd_fp8(*codes, scales, causal=causal, scale=math.log(2.0))
+    q8, k8, v8 = codes8
+    Or, lr = attention_fp64(q8, k8, v8, math.log(2.0), causal, "e4m3", descale=scales)
+    PV, _ = attention_fp64(q8, k8, v8 & 0x7F, math.log(2.0), causal, "e4m3", descale=scales)
+    bound = half_ulp(Or, "bf16") + (2 * (N + 128) * 2.0 ** -24 + 1e-5) * PV
+    assert np.all(np.abs(to_host64(o) - Or) <= bound)
+    assert np.max(np.abs(to_host64(lse) - lr)) <= 1e-3
+    bn = [t.transpose(1, 2).contiguous() for t in codes]
+    o2, lse2 = qa.fwd_fp8(*bn, scales, causal=causal, scale=math.log(2.0), layout="bnhd")
+    assert torch.equal(o2.transpose(1, 2).contiguous().view(torch.int16), o.view(torch.int16))
+    assert torch.equal(lse2.view(torch.int32), lse.view(torch.int32))
+
+
+@pytest.mark.parametrize("B,H,N,d,dtype", [(2, 160, 500, 64, "bf16"), (2, 130, 700, 128, "f16")])
+def test_tile_sizes_agree_on_full_grids(qa, B, H, N, d, dtype):
+    """Grids past the key groups' rules, where a forced tile size does choose
+    between 128- and 256-row workgroups: the same bytes."""
+    import torch
+    print(f"case full grid tiles {B}x{H}x{N}x{d} {dtype}", flush=True)
+    tq, tk, tv = (to_device(x, dtype) for x in si.make_qkv(B, H, N, d, dtype, seed=610 + N))
+    try:
+        for causal in (False, True):
+            res = []
+            for rows in (128, 256, 0):
+                qa.set_tile_rows(rows)
+                res.append(qa.fwd(tq, tk, tv, causal=causal))
+            for o, lse in res[1:]:
+                assert torch.equal(o.view(torch.int16), res[0][0].view(torch.int16))
+                assert torch.equal(lse.view(torch.int32), res[0][1].view(torch.int32))
+    finally:
+        qa.set_tile_rows(0)
