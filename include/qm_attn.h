@@ -237,17 +237,14 @@ int qm_attn_fwd_fp8_layout(const void* q, const void* k, const void* v, void* o,
  *            workgroups (eight wavefronts, one per CU) keep each K/V block in
  *            LDS for the most rows; 128-row workgroups (four wavefronts, two
  *            per CU) overlap one workgroup's start and end with the other's
- *            work, and run when N <= 2048 (FP8: N <= 4096, where its
- *            four-wavefront workgroups keep four-block K/V rings) or when
- *            the 256-row workgroups,
- *            dealt out in rounds over the device's CUs, would keep them less
- *            than 80% busy (fewer workgroups than CUs, or 1.5 rounds' worth).
- *   rows = 128 or 256: that size wherever it exists ([B][H][N][d] tensors with
- *            head dimension 64 or 128; everything else runs 256).
+ *            work, and run for short sequences (N <= 1024, causal 2048, d = 64
+ *            and FP8 4096) or when the 256-row workgroups, dealt out in rounds
+ *            over the device's CUs, would leave too many of them idle.
+ *   rows = 128 or 256: that size.
  *
- * Calls whose query blocks all fit the device at once (a few heads, N >= 384)
- * run workgroups of 64 or 128 rows that split the keys between their
- * wavefronts, whatever this setting is.
+ * Calls whose query blocks all fit the device at once (a few heads, N >= 384,
+ * equal head dimensions) run workgroups of 64 or 128 rows that split the keys
+ * between their wavefronts, whatever this setting is.
  *
  * Results do not depend on it: every query row takes the same arithmetic in
  * the same order, so outputs are byte-identical either way; only speed

@@ -25,7 +25,8 @@ LIB_NAME = "libqm_attn.so"
 LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 DEBUG_LIB_PATH = os.path.join(PKG_DIR, "libqm_attn_debug.so")
 
-SOURCES = ["qm_attn.cpp", "attn_fwd_gfx950.hip", "attn_fwd_split_gfx950.hip"]
+SOURCES = ["qm_attn.cpp", "attn_fwd_gfx950.hip", "attn_fwd_split_gfx950.hip",
+           "attn_fwd_rows128_gfx950.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -47,4 +47,7 @@ int key_groups(const AttnArgs& a, int cus);
 // Enqueues the instance with `groups` (2 or 4) key groups.
 hipError_t launch_attn_fwd_split(const AttnArgs& a, int groups, hipStream_t stream);
 
+// Enqueues a 128-row instance for 192-wide keys or the [B][N][heads][width] layout.
+hipError_t launch_attn_fwd_rows128(const AttnArgs& a, hipStream_t stream);
+
 }  // namespace qm
