@@ -98,6 +98,8 @@ def _declare(lib: ctypes.CDLL) -> ctypes.CDLL:
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """Load (once) and return the HIP library; raise if it has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib
@@ -179,49 +181,39 @@ def fwd_fp8(q, k, v, scales, causal: bool = False, scale: float | None = None, o
     if layout not in ("bhnd", "bnhd"):
         raise ValueError(f"layout must be 'bhnd' or 'bnhd', not {layout!r}")
     bnhd = layout == "bnhd"
-    names = "[B, N, H, d]" if bnhd else "[B, H, N, d]"
-
-    def shape(t):   # (B, heads, N, d) whatever the layout
-        s = tuple(t.shape)
-        return (s[0], s[2], s[1], s[3]) if bnhd else s
-
+    device = q.device
     for t in (q, k, v):
         if t.dim() != 4:
+            names = "[B, N, H, d]" if bnhd else "[B, H, N, d]"
             raise ValueError(f"q, k and v must have shape {names}")
         if t.dtype not in (torch.uint8, torch.float8_e4m3fn):
             raise TypeError("FP8 inputs must be float8_e4m3fn or uint8 codes")
-        if not t.is_cuda or t.device != q.device or not t.is_contiguous():
+        if not t.is_cuda or t.device != device or not t.is_contiguous():
             raise ValueError("q, k and v must be contiguous tensors on one ROCm device")
-    if shape(v) != shape(k) or shape(k)[0] != shape(q)[0] or shape(k)[2:] != shape(q)[2:]:
+    if bnhd:
+        B, N, H, d = q.shape
+        Bk, Nk, Hkv, dk = k.shape
+    else:
+        B, H, N, d = q.shape
+        Bk, Hkv, Nk, dk = k.shape
+    if v.shape != k.shape or Bk != B or Nk != N or dk != d:
         raise ValueError("k and v must hold Hkv heads matching q in B, N and d")
-    B, H, N, d = shape(q)
-    Hkv = shape(k)[1]
-    if scale is None:
-        scale = float(torch.tensor(1.0 / d ** 0.5, dtype=torch.float32))
+    scale = 1.0 / d ** 0.5 if scale is None else float(scale)   # rounded to float32 by the call
     if out is None:
-        out = torch.empty(tuple(q.shape), dtype=torch.bfloat16, device=q.device)
+        out = q.new_empty(q.shape, dtype=torch.bfloat16)
     elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
         raise ValueError("out must be a contiguous bfloat16 tensor shaped like q")
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    elif lse.shape != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
-        raise ValueError("lse must be a contiguous float32 tensor of shape [B, H, N]")
-    _check_outputs_on(q.device, out, lse)
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
+    lse = _lse(q, lse, B, H, N)
+    _check_outputs_on(device, out, lse)
     qs, ks, vs = (float(t) for t in scales)
-    with torch.cuda.device(q.device):
-        if bnhd or Hkv != H:
-            status = qm_attn_fwd_fp8_layout(q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                            out.data_ptr(), lse.data_ptr(), B, H, Hkv, N, d,
-                                            qs, ks, vs, scale, 1 if causal else 0,
-                                            stream.cuda_stream, QM_BNHD if bnhd else QM_BHND)
-        else:
-            status = qm_attn_fwd_fp8(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                     lse.data_ptr(), B, H, N, d, qs, ks, vs, scale,
-                                     1 if causal else 0, stream.cuda_stream)
-    if status != QM_OK:
-        raise QmAttnError(status, strerror(status))
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), B, H)
+    if bnhd or Hkv != H:
+        _enqueue(load_library().qm_attn_fwd_fp8_layout, device, stream,
+                 args + (Hkv, N, d, qs, ks, vs, scale, 1 if causal else 0),
+                 (QM_BNHD if bnhd else QM_BHND,))
+    else:
+        _enqueue(load_library().qm_attn_fwd_fp8, device, stream,
+                 args + (N, d, qs, ks, vs, scale, 1 if causal else 0), ())
     return out, lse
 
 
@@ -240,6 +232,31 @@ def _check_outputs_on(device, out, lse) -> None:
     for name, t in (("out", out), ("lse", lse)):
         if not t.is_cuda or t.device != device:
             raise ValueError(f"{name} must be on the inputs' device {device}, not {t.device}")
+
+
+def _lse(q, lse, B, H, N):
+    """The log-sum-exp output: the caller's, checked, or a new tensor."""
+    import torch
+    if lse is None:
+        return q.new_empty((B, H, N), dtype=torch.float32)
+    if lse.shape != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
+        raise ValueError("lse must be a contiguous float32 tensor of shape [B, H, N]")
+    return lse
+
+
+def _enqueue(entry, device, stream, before, after) -> None:
+    """Call a C entry point (arguments before and after its stream) with `device`
+    current, on `stream` (a torch stream; None: the device's current one)."""
+    import torch
+    index = device.index
+    raw = torch._C._cuda_getCurrentRawStream(index) if stream is None else stream.cuda_stream
+    if index == torch.cuda.current_device():
+        status = entry(*before, raw, *after)
+    else:
+        with torch.cuda.device(index):
+            status = entry(*before, raw, *after)
+    if status != QM_OK:
+        raise QmAttnError(status, strerror(status))
 
 
 def _dtype_code(t) -> int:
@@ -270,64 +287,50 @@ def fwd(q, k, v, causal: bool = False, scale: float | None = None, out=None, lse
     if layout not in ("bhnd", "bnhd"):
         raise ValueError(f"layout must be 'bhnd' or 'bnhd', not {layout!r}")
     bnhd = layout == "bnhd"
-    names = "[B, N, H, d]" if bnhd else "[B, H, N, d]"
     if q.dim() != 4:
-        raise ValueError(f"q must have shape {names}")
-
-    def shape(t):   # (B, heads, N, width) whatever the layout
-        s = tuple(t.shape)
-        return (s[0], s[2], s[1], s[3]) if bnhd else s
-
-    if k.dim() != 4 or v.dim() != 4 or shape(v)[:3] != shape(k)[:3]:
+        raise ValueError(f"q must have shape {'[B, N, H, d]' if bnhd else '[B, H, N, d]'}")
+    # a head's rows lie along `rows`, heads along `heads`
+    rows, heads = (1, 2) if bnhd else (2, 1)
+    qs, ks, vs = q.shape, k.shape, v.shape
+    if len(ks) != 4 or len(vs) != 4 or vs[:3] != ks[:3]:
         raise ValueError("k must hold Hkv heads of width d and v Hkv heads of width dv")
-    if shape(k)[0] != shape(q)[0] or shape(k)[2:] != shape(q)[2:]:
+    B, H, N, d = qs[0], qs[heads], qs[rows], qs[3]
+    Hkv, dv = ks[heads], vs[3]
+    if ks[0] != B or ks[rows] != N or ks[3] != d:
         raise ValueError("k must match q in B, N and d")
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("q, k and v must be on a ROCm device")
-    if not (q.device == k.device == v.device):
+    device = q.device
+    if not (device == k.device == v.device):
         raise ValueError("q, k and v must be on the same device")
     if not (q.dtype == k.dtype == v.dtype):
         raise TypeError("q, k and v must have the same dtype")
     if not (q.is_contiguous() and k.is_contiguous() and v.is_contiguous()):
+        names = "[B, N, H, d]" if bnhd else "[B, H, N, d]"
         raise ValueError(f"q, k and v must be contiguous {names}")
-    B, H, N, d = shape(q)
-    dv = shape(v)[3]
-    Hkv = shape(k)[1]
     code = _dtype_code(q)
-    if scale is None:
-        scale = float(torch.tensor(1.0 / d ** 0.5, dtype=torch.float32))
-    oshape = (B, N, H, dv) if bnhd else (B, H, N, dv)
+    # the C float argument rounds the scale to float32
+    scale = 1.0 / d ** 0.5 if scale is None else float(scale)
     if out is None:
-        out = torch.empty(oshape, dtype=q.dtype, device=q.device)
-    elif tuple(out.shape) != oshape or out.dtype != q.dtype or not out.is_contiguous():
-        raise ValueError(f"out must be a contiguous {list(oshape)} tensor of q's dtype")
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    elif lse.shape != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
-        raise ValueError("lse must be a contiguous float32 tensor of shape [B, H, N]")
-    _check_outputs_on(q.device, out, lse)
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    with torch.cuda.device(q.device):
-        if bnhd:
-            status = qm_attn_fwd_layout(q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                        out.data_ptr(), lse.data_ptr(), B, H, Hkv, N, d, dv,
-                                        scale, 1 if causal else 0, stream.cuda_stream, code,
-                                        QM_BNHD)
-        elif dv != d:
-            if Hkv != H:
-                raise ValueError("unequal head dimensions need as many key/value heads as query heads")
-            status = qm_attn_fwd_mla(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                     lse.data_ptr(), B, H, N, d, dv, scale, 1 if causal else 0,
-                                     stream.cuda_stream, code)
-        elif Hkv == H:
-            status = qm_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                 lse.data_ptr(), B, H, N, d, scale, 1 if causal else 0,
-                                 stream.cuda_stream, code)
-        else:
-            status = qm_attn_fwd_gqa(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                     lse.data_ptr(), B, H, Hkv, N, d, scale,
-                                     1 if causal else 0, stream.cuda_stream, code)
-    if status != QM_OK:
-        raise QmAttnError(status, strerror(status))
+        out = q.new_empty(qs[:3] + (dv,))
+    else:
+        oshape = (*qs[:3], dv)
+        if tuple(out.shape) != oshape or out.dtype != q.dtype or not out.is_contiguous():
+            raise ValueError(f"out must be a contiguous {list(oshape)} tensor of q's dtype")
+    lse = _lse(q, lse, B, H, N)
+    _check_outputs_on(device, out, lse)
+    lib = load_library()
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), B, H)
+    causal = 1 if causal else 0
+    if bnhd:
+        _enqueue(lib.qm_attn_fwd_layout, device, stream, args + (Hkv, N, d, dv, scale, causal),
+                 (code, QM_BNHD))
+    elif dv != d:
+        if Hkv != H:
+            raise ValueError("unequal head dimensions need as many key/value heads as query heads")
+        _enqueue(lib.qm_attn_fwd_mla, device, stream, args + (N, d, dv, scale, causal), (code,))
+    elif Hkv == H:
+        _enqueue(lib.qm_attn_fwd, device, stream, args + (N, d, scale, causal), (code,))
+    else:
+        _enqueue(lib.qm_attn_fwd_gqa, device, stream, args + (Hkv, N, d, scale, causal), (code,))
     return out, lse
