@@ -24,9 +24,8 @@ hipError_t launch_instance(const AttnArgs& a, const Device& dev, hipStream_t str
   constexpr size_t lds = lds_bytes<DK, DV, DT, WAVES>();
   constexpr int per_cu = wgs_per_cu<DK, WAVES>();
   static_assert(lds * per_cu <= 160 * 1024, "the workgroups of a CU fit its LDS");
-  // FP8: one workgroup per tile (see attn_fwd_body)
   return launch_tiles<attn_fwd_kernel<DK, DV, DT, CAUSAL, WAVES>>(
-      a, dev, 32 * WAVES, 64 * WAVES, lds, per_cu, !Ops<DT>::kFp8, stream);
+      a, dev, 32 * WAVES, 64 * WAVES, lds, per_cu, stream);
 }
 
 template <int DK, int DV, int DT, int WAVES>

@@ -37,9 +37,9 @@ hipError_t launch_masks(const AttnArgs& a, const Device& dev, hipStream_t stream
   constexpr size_t lds = lds_bytes<DK, DV, DT, 4>();
   static_assert(lds * per_cu<DK>() <= 160 * 1024, "the workgroups of a CU fit its LDS");
   return a.causal ? launch_tiles<attn_fwd_rows128_kernel<DK, DV, DT, true, LAYOUTS>>(
-                        a, dev, 128, 256, lds, per_cu<DK>(), DT != 2, stream)
+                        a, dev, 128, 256, lds, per_cu<DK>(), stream)
                   : launch_tiles<attn_fwd_rows128_kernel<DK, DV, DT, false, LAYOUTS>>(
-                        a, dev, 128, 256, lds, per_cu<DK>(), DT != 2, stream);
+                        a, dev, 128, 256, lds, per_cu<DK>(), stream);
 }
 
 }  // namespace

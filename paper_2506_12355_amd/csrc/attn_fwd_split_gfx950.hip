@@ -36,9 +36,9 @@ hipError_t launch_masks(const AttnArgs& a, const Device& dev, hipStream_t stream
   constexpr size_t lds = lds_bytes<DK, DV, DT, 8 / G, G>();
   static_assert(lds <= 160 * 1024, "a workgroup's rings fit the LDS");
   return a.causal ? launch_tiles<attn_fwd_split_kernel<DK, DV, DT, true, G, LAYOUTS>>(
-                        a, dev, 256 / G, 512, lds, 1, true, stream)
+                        a, dev, 256 / G, 512, lds, 1, stream)
                   : launch_tiles<attn_fwd_split_kernel<DK, DV, DT, false, G, LAYOUTS>>(
-                        a, dev, 256 / G, 512, lds, 1, true, stream);
+                        a, dev, 256 / G, 512, lds, 1, stream);
 }
 
 template <int DK, int DV, int DT, int G>
