@@ -10,7 +10,8 @@
 // sequence in blocks of BN = 64 keys (the loop of the paper's Appendix B
 // listings).  A K/V block staged in LDS serves all 256 rows.  For short
 // sequences the same kernel runs with four wavefronts (BM = 128) and several
-// workgroups per CU (see ring_depth, wgs_per_cu and launch_attn_fwd).
+// workgroups per CU (see ring_depth, wgs_per_cu and choose_waves); on the
+// smallest grids its eight wavefronts form key groups (see key_groups).
 //
 // The two products use the 32x32x16 MFMA of CDNA4 (FP8 inputs: the 32x32x64
 // one, with ds_read_b64_tr_b8 for V^T and E4M3 packs for P^T; see Fp8 below):
@@ -59,7 +60,8 @@
 // Causal masking: key blocks entirely above the diagonal of the workgroup are
 // never loaded; a wavefront skips the blocks entirely above its own rows;
 // elementwise masking runs only on blocks that straddle the diagonal or the
-// sequence tail.  A workgroup runs a long and a short query block, the long
+// sequence tail.  Where the query blocks are more than run at once, a
+// workgroup runs them in pairs, a long and a short query block, the long
 // one first, so that all workgroups cost the same.
 //
 // Runs (a query block of one head) follow one another in a workgroup, and the
@@ -679,11 +681,11 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
     const int v8_base = VOFF + (4 * (grp >> 1) + ((sl >> 1) & 3)) * LV::VGS +
                         (sl >> 3) * LV::ROW + 16 * (grp & 1) + 8 * (sl & 1);
 
-    auto k_read = [&](int kb, int kt, int ks) {
+    auto k_read_at = [&](const char* ring, int kb, int kt, int ks) __attribute__((always_inline)) {
       constexpr int KSB = OP::KSTEP * ES;   // bytes per k-step of a row
       const char* a = (ks < KT::NKS0)
-          ? lds + kb * KT::BYTES + k_base0 + kt * (32 / KT::L0::NG) * KT::L0::ROW + KSB * ks
-          : lds + kb * KT::BYTES + k_base1 + kt * (32 / KT::L1::NG) * KT::L1::ROW +
+          ? ring + kb * KT::BYTES + k_base0 + kt * (32 / KT::L0::NG) * KT::L0::ROW + KSB * ks
+          : ring + kb * KT::BYTES + k_base1 + kt * (32 / KT::L1::NG) * KT::L1::ROW +
                 KSB * (ks - KT::NKS0);
       if constexpr (FP8) {
         const u32x4 lo = *reinterpret_cast<const u32x4*>(a);
@@ -693,6 +695,9 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
       } else {
         return *reinterpret_cast<const u32x4*>(a);
       }
+    };
+    auto k_read = [&](int kb, int kt, int ks) __attribute__((always_inline)) {
+      return k_read_at(lds, kb, kt, ks);
     };
     auto v_read = [&](int vb, int mt, int u, int h2) {
       // group of key 16 u + 8 h2 + kq is (16 u + 8 h2) % NG + kq, slot (16 u + 8 h2) / NG
@@ -736,14 +741,14 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
       }
     };
 
-    // GEMM-I: two 32-key tiles of S^T for the block in K buffer kb
-    auto gemm1 = [&](int kb, f32x16 (&s)[2]) {
+    // GEMM-I: two 32-key tiles of S^T for the block in K buffer kb of a ring
+    auto gemm1 = [&](const char* ring, int kb, f32x16 (&s)[2]) __attribute__((always_inline)) {
       s[0] = f32x16{};
       s[1] = f32x16{};
   #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) {
   #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) s[kt] = OP::mfma(k_read(kb, kt, ks), qf[ks], s[kt]);
+        for (int kt = 0; kt < 2; ++kt) s[kt] = OP::mfma(k_read_at(ring, kb, kt, ks), qf[ks], s[kt]);
       }
     };
 
@@ -1024,7 +1029,29 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
       }
     }
     __syncthreads();
-    if (j_act > 0) gemm1(0, sa);
+    if constexpr (G > 1 && FP8) {
+      // The other groups start from block 0's row maximum, as group 0 does after
+      // its first block (its K is in group 0's slot 0): E4M3 weights are then
+      // rounded against the same maximum in every group, and as in an unsplit
+      // run.  Each from its own first block, they differed from an unsplit
+      // run's O by 3.2% (four groups, unmasked), no closer to the exact values.
+      if (kgrp > 0 && j_act > 0) {
+        gemm1(lds0, 0, sb);
+        const bool need_mask = kBN > N || (CAUSAL && kBN - 1 > qw);
+        if (need_mask) {
+  #pragma unroll
+          for (int kt = 0; kt < 2; ++kt) {
+  #pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int key = 32 * kt + 8 * (r / 4) + 4 * hi + (r % 4);
+              if (key >= N || (CAUSAL && key > qrow)) sb[kt][r] = -INFINITY;
+            }
+          }
+        }
+        m_run = fmaxf(m_run, row_max(sb) * p.c);
+      }
+    }
+    if (j_act > 0) gemm1(lds, 0, sa);
     __syncthreads();   // K slot 0 is refilled by block 0
 
     using C0 = std::integral_constant<int, 0>;

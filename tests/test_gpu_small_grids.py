@@ -115,3 +115,40 @@ def test_tile_sizes_agree_on_full_grids(qa, B, H, N, d, dtype):
                 assert torch.equal(lse.view(torch.int32), res[0][1].view(torch.int32))
     finally:
         qa.set_tile_rows(0)
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d,dv,dtype,layout,rows", [
+    (1, 3, 3, 1100, 64, 64, "bf16", 0, 0),     # four key groups
+    (1, 3, 1, 2177, 128, 128, "f16", 1, 0),    # two key groups, two-block rings
+    (1, 9, 9, 1300, 64, 64, "f16", 0, 0),      # two key groups, four-block rings
+    (1, 48, 48, 900, 128, 128, "bf16", 1, 0),  # 128-row [B][N][H][d]
+    (1, 5, 5, 900, 192, 128, "bf16", 0, 0),    # 128-row, 192-wide keys
+    (2, 80, 80, 900, 64, 64, "bf16", 0, 256),  # eight waves, deferred second product
+])
+def test_checking_build_gives_the_same_bytes(qa, B, H, Hkv, N, d, dv, dtype, layout, rows):
+    """The build with a barrier per key block agrees on the small grids' routes, whose
+    groups share barriers and exchange results through the rings' LDS."""
+    import torch
+    print(f"case checking build {B}x{H}x{N}x{d} {dtype} layout={layout}", flush=True)
+    libs = (qa.load_library(), qa.open_library(qa.DEBUG_LIB_PATH))
+    tq, tk, tv = (to_device(x, dtype) for x in si.make_qkv(B, H, N, d, dtype, seed=710 + N, Hkv=Hkv, dv=dv))
+    if layout:
+        tq, tk, tv = (t.transpose(1, 2).contiguous() for t in (tq, tk, tv))
+    try:
+        for causal in (0, 1):
+            res = []
+            for lib in libs:
+                assert lib.qm_attn_set_tile_rows(rows) == 0
+                o = torch.full((B, N, H, dv) if layout else (B, H, N, dv), float("nan"),
+                               dtype=tq.dtype, device="cuda")
+                lse = torch.full((B, H, N), float("nan"), device="cuda")
+                assert lib.qm_attn_fwd_layout(
+                    tq.data_ptr(), tk.data_ptr(), tv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H,
+                    Hkv, N, d, dv, si.default_scale(d), causal,
+                    torch.cuda.current_stream().cuda_stream, 0 if dtype == "f16" else 1, layout) == 0
+                torch.cuda.synchronize()
+                res.append((o.view(torch.int16), lse.view(torch.int32)))
+            assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    finally:
+        for lib in libs:
+            lib.qm_attn_set_tile_rows(0)
