@@ -237,8 +237,8 @@ int qm_attn_fwd_fp8_layout(const void* q, const void* k, const void* v, void* o,
  *            workgroups (eight wavefronts, one per CU) keep each K/V block in
  *            LDS for the most rows; 128-row workgroups (four wavefronts, two
  *            per CU) overlap one workgroup's start and end with the other's
- *            work, and run for short sequences (N <= 1024, causal 2048, FP8
- *            4096, d = 64 4096 and causal 16384) or when the 256-row workgroups, dealt out in rounds
+ *            work, and run for short sequences (N <= 1024, causal 2048, d = 64
+ *            and FP8 4096) or when the 256-row workgroups, dealt out in rounds
  *            over the device's CUs, would leave too many of them idle.
  *   rows = 128 or 256: that size.
  *

@@ -60,15 +60,9 @@ int choose_waves(const AttnArgs& a, int cus) {
   }
   // Short sequences, us, 256 -> 128 rows at a full grid: d = 128 bf16 N = 1024
   // 133 -> 131, N = 2048 233 -> 238, causal 145 -> 142, N = 4096 440 -> 457 and
-  // 247 -> 247; d = 64 N = 2048 146 -> 138, N = 4096 274 -> 267, N = 8192
-  // 1046 -> 1078 (H = 32 B = 2), causal N = 8192 560 -> 548, N = 16384
-  // 1078 -> 1070; FP8 N = 4096 282 -> 280, causal 165 -> 161, N = 8192
-  // 1044 -> 1084.
-  const int line = a.d == 64 ? (a.causal ? 16384 : 4096)
-                   : a.dtype == 2 ? 4096
-                   : a.causal ? 2048
-                              : 1024;
-  if (a.N <= line) return 4;
+  // 247 -> 247; d = 64 N = 2048 146 -> 138, N = 4096 274 -> 267, causal
+  // 156 -> 150; FP8 N = 4096 282 -> 280, causal 165 -> 161.
+  if (a.N <= (a.d == 64 || a.dtype == 2 ? 4096 : a.causal ? 2048 : 1024)) return 4;
   // Longer ones: a 256-row tile takes its CU 20 units of time, two 128-row
   // tiles side by side 21, a 128-row tile that has a CU to itself 14.  (B=3 H=32
   // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
