@@ -73,7 +73,8 @@ enum {
   QM_ERR_NULL = -1,        /* q, k, v, o or lse is NULL */
   QM_ERR_SHAPE = -2,       /* B, H or N < 1, Hkv not a divisor of H, B*H*N*d
                               does not fit in 62 bits, or (N + 256) * d (QM_BNHD:
-                              times the heads, in bytes) does not fit in 31 (32) bits */
+                              times the heads, in bytes of q, k and v) does not fit
+                              in 31 (32) bits */
   QM_ERR_HEADDIM = -3,     /* d is not 64 or 128 (qm_attn_fwd_mla: (d_qk, d_v) is not
                               (64, 64), (128, 128) or (192, 128)) */
   QM_ERR_DTYPE = -4,       /* dtype is not QM_F16 or QM_BF16 */

@@ -1114,8 +1114,17 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
     // the output is 16-bit for every input type (FP8 inputs give bf16)
     using OutT = Half<FP8 ? 1 : DT>;
     const int b = bh / p.H;
+    // O's rows of this head: from row o_row0 on, o_rows of them.  The front end
+    // keeps the inputs' byte offsets within 32 bits; FP8's bf16 O has rows twice
+    // as wide, so with interleaved heads a whole head's could wrap (H = 64 beyond
+    // 2^18 tokens): there the buffer is the query block's own rows.  (Key groups
+    // run only where all query blocks fit the device at once: a small O.)
+    constexpr bool kWideO = FP8 && LAYOUTS != kBhndOnly && G == 1;
+    const int o_row0 = kWideO ? qb * BM : 0;
+    const int o_rows = kWideO ? min(BM, N - o_row0) : N;
     const __amdgpu_buffer_rsrc_t ro =
-        make_rsrc(p.o + head_off(b, bh - b * p.H, p.H, WO) / 2, span(rs_o, WO));
+        make_rsrc(p.o + (head_off(b, bh - b * p.H, p.H, WO) + (size_t)o_row0 * rs_o) / 2,
+                  (uint32_t)(o_rows - 1) * rs_o + WO);
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(p.lse + (size_t)bh * N, (uint32_t)N * 4);
     // the lane's quads of O: quad qd holds columns 32 (qd / 4) + 8 (qd % 4) + 4 hi .. + 3
     constexpr int NQ = 4 * NMT;
@@ -1210,7 +1219,13 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
     // other half's odd quad gives lanes 0-31 columns 8 g .. 8 g + 7 of their
     // row and lanes 32-63 columns 8 (g + 1) .. 8 (g + 1) + 7 of theirs.
     const float inv = p.vscale / l;
-    const uint32_t o_off = (uint32_t)qrow * rs_o + (uint32_t)(kgrp * OWN * 16 + hi * 16);
+    uint32_t o_row = (uint32_t)qrow * rs_o;
+    if constexpr (kWideO) {
+      // rows past the end of the sequence, whose products may wrap, go past the
+      // end of any buffer (at most 2^32 - 2^24 bytes here)
+      o_row = qrow < N ? (uint32_t)(wave * 32 + l32) * rs_o : 0xfffffe00u;
+    }
+    const uint32_t o_off = o_row + (uint32_t)(kgrp * OWN * 16 + hi * 16);
   #pragma unroll
     for (int i = 0; i < OWN; i += 2) {
       u32x4 w;

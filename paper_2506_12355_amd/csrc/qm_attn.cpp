@@ -66,7 +66,8 @@ int attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, i
   if (layout != QM_BHND && !(layout == QM_BNHD && d == dv)) return QM_ERR_LAYOUT;
   if (layout == QM_BNHD) {
     // rows of one head are max(H, Hkv) rows apart: the kernels' 32-bit byte
-    // offsets, including the padded last query block, must still fit
+    // offsets into q, k and v, including the padded last query block, must still
+    // fit (FP8's o, twice as wide, is addressed from its query block's first row)
     const uint64_t heads = (uint64_t)(H > Hkv ? H : Hkv);
     const uint64_t row = heads * (uint64_t)d * (dtype == kFp8 ? 1u : 2u);
     if (((uint64_t)N + 256) * row >= (1ull << 32)) return QM_ERR_SHAPE;

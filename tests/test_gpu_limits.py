@@ -5,6 +5,8 @@
   d = 128 (four 4 GiB tensors).  Inputs repeat with an odd period, so a row
   address that wrapped at any power of two would read different data.
 * One head of 2^20 + 17 tokens in ``[B][H][N][d]`` (d = 64, f16).
+* FP8 ``[B][N][H][d]`` where a head's rows of O, twice as wide as Q's, span
+  more than 2^32 bytes, and where the rows past a short sequence's end would.
 * Many small heads (3003 workgroups, not a multiple of the eight XCDs), and
   multi-query attention with 4096 query heads on one key/value head.
 
@@ -86,6 +88,45 @@ def test_one_head_of_a_million_tokens(qa):
         L = np.array([float(lse[b, h, i]) for b, h, i in rows])
         Or, lr = attention_rows_fp64(q, k, v, scale, causal, "f16", rows)
         check_close(O, L, Or, lr, "f16", f"long head N={N} causal={causal}")
+
+
+@pytest.mark.parametrize("H,N,rows", [
+    (20000, 1000, 128),     # a head's O spans 5.1e9 bytes: live rows past 2^32
+    (20000, 1000, 256),
+    (100000, 40, 0),        # 1.0e9 bytes of live rows, dead ones (up to row 127) at 3.3e9
+    (130000, 1, 256),       # dead rows of a 256-row block up to 8.5e9
+    (65535, 256, 256),      # the widest query block: 2^32 - 2^24 - 2^16 + 512 bytes
+])
+def test_fp8_bnhd_output_offsets_past_32_bits(qa, H, N, rows):
+    """The same bytes as [B][H][N][d], whose heads' offsets are small; the front
+    end's bound counts the one-byte inputs only."""
+    import torch
+    d = 128
+    assert (N + 256) * H * d < 1 << 32
+    _say(f"case FP8 BNHD wide O H={H} N={N} tile_rows={rows}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H + N)
+
+    def codes(heads):   # every E4M3 code but the two NaNs
+        x = torch.randint(0, 254, (1, heads, N, d), generator=gen, device="cuda", dtype=torch.uint8)
+        return x + (x >= 127).to(torch.uint8)
+
+    q, k, v = codes(H), codes(1), codes(1)
+    scales = (0.01, 0.01, 0.5)
+    bn = [t.transpose(1, 2).contiguous() for t in (q, k, v)]
+    try:
+        qa.set_tile_rows(rows)
+        for causal in (False, True):
+            o, lse = qa.fwd_fp8(q, k, v, scales, causal=causal)
+            out = torch.full((1, N, H, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            o2, lse2 = qa.fwd_fp8(*bn, scales, causal=causal, out=out, layout="bnhd")
+            assert bool(torch.isfinite(lse).all())
+            assert torch.equal(o2.transpose(1, 2).view(torch.int16), o.view(torch.int16))
+            assert torch.equal(lse2.view(torch.int32), lse.view(torch.int32))
+            del o, o2, out
+    finally:
+        qa.set_tile_rows(0)
+        torch.cuda.empty_cache()
 
 
 def test_many_small_heads(qa):
