@@ -98,6 +98,7 @@
 #include <type_traits>
 
 #include "attn_fwd_launch.h"
+#include "tile_order.h"
 
 namespace qm {
 namespace {
@@ -166,7 +167,8 @@ struct KParams {
   int group;        // H / Hkv: query heads per key/value head
   int nq;           // query blocks per head
   int paired;       // causal: a tile is a pair of query blocks (else one)
-  int down;         // causal, not paired: tiles per XCD that count query blocks down
+  int row;          // CUs per XCD when the tiles go in balanced order, else 0
+  int xcd_heads;    // heads per XCD where they are whole, else 0
   int wg_per_head;  // tiles per head: nq, or ceil(nq / 2) when paired
   int total;        // wg_per_head * B * H tiles
   float c;     // |scale| * log2 e (FP8: |scale * q_scale * k_scale| * log2 e)
@@ -458,16 +460,19 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
   // A tile is one (batch*head, query block), or, causal, the pair (nq-1-i, i)
   // of query blocks (query block qb costs qb + 1 units of key blocks, so every
   // pair costs the same and the grid has no long tail; the longer runs first).
-  // Where all causal query blocks run at once they stay single: the longest
-  // alone is shorter than a pair, and one's prologue runs beside another's
-  // blocks.  The first p.down tiles of an XCD count a head's query blocks down
-  // and the others up, so that the two blocks a CU may hold (one from each half
-  // of the XCD's tiles) complement each other.
+  // Where all causal query blocks run at once they stay single, a head's longest
+  // first: the longest alone is shorter than a pair, and one's prologue runs
+  // beside another's blocks.  Where a CU then holds several they go in balanced
+  // order (tile_order.h).
   // Workgroup w walks tiles w, w + grid, ...: the grid holds as many workgroups
   // as the CUs run at once (a multiple of 8), so the launch gap and set-up of a
   // new workgroup are paid once per CU, not per tile.
   const int per_xcd = p.total / kXcds;
   int tile = blockIdx.x;
+  // (only the instances that run several workgroups on a CU)
+  if constexpr (CAUSAL && G == 1 && WAVES == 4 && DK != 192) {
+    if (p.row) tile = balanced_tile(tile, p.total, p.row, p.nq, p.xcd_heads);
+  }
   int bh, qb;          // batch * head and query block of the current run
   int qb2 = -1;        // causal: the query block this tile still has to run
   auto enter_tile = [&]() __attribute__((always_inline)) {
@@ -478,7 +483,7 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
     if (CAUSAL) {
       const int other = p.nq - 1 - qb;
       if (p.paired) qb2 = qb != other ? qb : -1;
-      if (p.paired || tile / kXcds < p.down) qb = other;
+      qb = other;
     }
   };
 
@@ -1262,9 +1267,9 @@ __device__ __forceinline__ void attn_fwd_body(const KParams& p) {
 // Causal query blocks stay single (see attn_fwd_body) when each has a CU to
 // itself, or, up to N = 2048, when all are resident.  Measured against pairs
 // (d = 128 bf16, B = 1, us): N = 250 H = 8 15.2 -> 9.4, N = 512 H = 64
-// 19.1 -> 13.5, N = 2048 H = 16 37.4 -> 33.8; two workgroups per CU: N = 1000
-// H = 64 27.3 -> 25.4, N = 2048 H = 32 42.0 -> 42.1, N = 4096 H = 16
-// 78.3 -> 78.8, N = 8192 H = 8 142.6 -> 148.0.
+// 19.1 -> 13.5, N = 2048 H = 16 37.4 -> 33.8; two workgroups per CU, in balanced
+// order: N = 1024 H = 40 25.6 -> 22.1, N = 2048 H = 24 38.0 -> 36.6, H = 32
+// 41.3 -> 41.4; beyond 2048 (H = 16, 8): N = 4096 78.3 -> 78.8, 8192 142.6 -> 148.0.
 inline KParams make_params(const AttnArgs& a, int bm, int cus, int resident) {
   KParams kp;
   kp.q = static_cast<const uint8_t*>(a.q);
@@ -1281,8 +1286,8 @@ inline KParams make_params(const AttnArgs& a, int bm, int cus, int resident) {
   kp.paired = a.causal && blocks > cus && (a.N > 2048 || blocks > resident);
   kp.wg_per_head = kp.paired ? (kp.nq + 1) / 2 : kp.nq;
   kp.total = kp.wg_per_head * a.B * a.H;
-  // half of an XCD's tiles when whole heads fall in each half, else all
-  kp.down = kp.total % (2 * kXcds * kp.nq) == 0 ? kp.total / (2 * kXcds) : kp.total;
+  kp.row = a.causal && !kp.paired && blocks > cus ? cus / kXcds : 0;
+  kp.xcd_heads = (a.B * a.H) % kXcds ? 0 : a.B * a.H / kXcds;
   kp.c = a.c;
   kp.vscale = a.vscale;
   kp.qmode = a.qmode;

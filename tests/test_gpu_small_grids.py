@@ -33,6 +33,9 @@ def qa():
     (2, 8, 8, 1025, 64, "bf16"),      # whole heads per half, a last block of one row
     (1, 64, 8, 1000, 128, "bf16"),    # two query blocks to a CU
     (5, 13, 13, 1000, 64, "f16"),     # just under three to a CU
+    (1, 40, 8, 1000, 128, "f16"),     # whole heads per XCD, some CUs with two blocks
+    (1, 54, 18, 640, 64, "bf16"),     # heads shared between XCDs, blocks left over
+    (2, 80, 80, 200, 128, "bf16"),    # heads of two blocks
     (3, 33, 33, 700, 128, "bf16"),    # past what is resident: pairs
 ])
 def test_causal_small_grid_matches_oracle(qa, B, H, Hkv, N, d, dtype):
