@@ -1,5 +1,5 @@
-// The instances of the attention kernel (attn_fwd_kernel.h) and the choice of
-// one per call: eight wavefronts (256 query rows, one workgroup per CU) or four
+// The instances of the attention kernel (attn_fwd_kernel.h), of which a call runs
+// the one that attn_fwd_rules.h gives: eight wavefronts (256 query rows, one workgroup per CU) or four
 // (128 rows, two or three workgroups per CU); the smallest grids and the 128-row
 // instances for other tensors are in files of their own.
 
@@ -7,6 +7,7 @@
 
 #include "attn_fwd_launch.h"
 #include "attn_fwd_kernel.h"
+#include "attn_fwd_rules.h"
 
 namespace qm {
 namespace {
@@ -38,36 +39,6 @@ template <int DK, int DV, int DT>
 hipError_t launch_waves(const AttnArgs& a, const Device& dev, int waves, hipStream_t stream) {
   return waves == 4 ? launch_masks<DK, DV, DT, 4>(a, dev, stream)
                     : launch_masks<DK, DV, DT, 8>(a, dev, stream);
-}
-
-// Eight waves keep K/V tiles in LDS for the most rows; four let one workgroup's
-// prologue and epilogue run beside another's key loop, which wins where
-// workgroups are short, and where the 256-row tiles, dealt out in rounds over
-// the CUs, would leave too many of them idle.
-int choose_waves(const AttnArgs& a, int cus) {
-  const auto tiles = [&](int rows) {
-    const long long nq = (a.N + rows - 1) / rows;
-    return (a.causal ? (nq + 1) / 2 : nq) * a.B * a.H;
-  };
-  const long long rounds8 = (tiles(256) + cus - 1) / cus, rounds4 = (tiles(128) + cus - 1) / cus;
-  // 192-wide keys run one workgroup of either size per CU: four waves where all
-  // of theirs run at once (H = 16 N = 4096 causal 104.8 -> 85.6 us; in two
-  // rounds, H = 8 N = 8192 unmasked, 270 -> 300).  Short causal pairs gain
-  // nothing (H = 128 N = 512 23.5 -> 23.9), single query blocks do.
-  if (a.d == 192) {
-    const long long blocks = (long long)((a.N + 127) / 128) * a.B * a.H;
-    return blocks <= cus || (a.N >= 768 && rounds4 == 1) ? 4 : 8;
-  }
-  // Short sequences, us, 256 -> 128 rows at a full grid: d = 128 bf16 N = 1024
-  // 133 -> 131, N = 2048 233 -> 238, causal 145 -> 142, N = 4096 440 -> 457 and
-  // 247 -> 247; d = 64 N = 2048 146 -> 138, N = 4096 274 -> 267, causal
-  // 156 -> 150; FP8 N = 4096 282 -> 280, causal 165 -> 161.
-  if (a.N <= (a.d == 64 || a.dtype == 2 ? 4096 : a.causal ? 2048 : 1024)) return 4;
-  // Longer ones: a 256-row tile takes its CU 20 units of time, two 128-row
-  // tiles side by side 21, a 128-row tile that has a CU to itself 14.  (B=3 H=32
-  // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
-  // 192 tiles of 256 rows fill 192 CUs: 104 us with them, 109 with 384 halves.)
-  return rounds4 / 2 * 21 + rounds4 % 2 * 14 < rounds8 * 20 ? 4 : 8;
 }
 
 }  // namespace

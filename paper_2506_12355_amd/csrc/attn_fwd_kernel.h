@@ -135,7 +135,6 @@ constexpr float kPmax = 256.0f;
 // (an error O carries in full when that key dominates).  Rare for diffuse
 // rows; on near-one-hot rows it keeps O within 1e-2 plus half a bf16 ulp.
 constexpr float kDominant = 4.0f;
-constexpr int kXcds = 8;
 constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data
 // s_waitcnt immediate for vmcnt(0) and lgkmcnt(0): the direct LDS loads of
 // this wave have landed

@@ -1,11 +1,13 @@
 // Internal interface between the C-ABI front end (qm_attn.cpp) and the gfx950
-// kernels (attn_fwd_gfx950.hip).  Not installed; callers use include/qm_attn.h.
+// kernels (attn_fwd_*_gfx950.hip).  Not installed; callers use include/qm_attn.h.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
 namespace qm {
+
+constexpr int kXcds = 8;   // workgroup w of a launch runs on XCD w % kXcds
 
 // How the kernel conditions Q when it loads it into registers.  Both changes
 // are exact in 16-bit arithmetic, so the kernel can always use a positive
@@ -38,11 +40,6 @@ struct AttnArgs {
 // groups).  Arguments have been
 // validated by the caller.  Returns the HIP launch status.
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t stream);
-
-// Key groups of a workgroup (1, 2 or 4) that a call runs with on a device of
-// `cus` CUs.  A function of the shape, type and mask alone: not of tile_rows or
-// layout, on which results do not depend.
-int key_groups(const AttnArgs& a, int cus);
 
 // Enqueues the instance with `groups` (2 or 4) key groups.
 hipError_t launch_attn_fwd_split(const AttnArgs& a, int groups, hipStream_t stream);

@@ -1,0 +1,71 @@
+// Which instance of the attention kernel a call runs, from its shape, type and mask
+// and the device's CU count: host code only.
+#pragma once
+
+#include "attn_fwd_launch.h"
+
+namespace qm {
+
+// Key groups of a workgroup (1, 2 or 4) that a call runs with on a device of
+// `cus` CUs.  A function of the shape, type and mask alone: not of tile_rows or
+// layout, on which results do not depend.
+inline int key_groups(const AttnArgs& a, int cus) {
+  if (a.d == 192) return 1;
+  // Workgroups of query blocks of `rows` rows, causal ones in pairs where they
+  // are too many to stay single (which pays from N = 4096 on).
+  const auto fits = [&](int rows) {
+    const long long nq = (a.N + rows - 1) / rows;
+    const long long heads = (long long)a.B * a.H;
+    return nq * heads <= cus || (a.causal && a.N >= 4096 && (nq + 1) / 2 * heads <= cus);
+  };
+  // All query blocks in one round of one workgroup per CU: in two rounds the
+  // split loses to two unsplit workgroups per CU (0.6-0.9x).  Below these
+  // lengths the merge (about 1 us) outweighs the steps saved; each line lies
+  // between the sizes named (us, unsplit -> split, B = 1, unmasked unless
+  // causal is said):
+  //   four groups: d = 64 N = 256 H = 8 6.05 -> 6.57, N = 512 8.31 -> 7.93;
+  //   FP8 N = 256 7.05 -> 7.67, N = 512 9.20 -> 8.91;
+  //   two groups, d = 64: N = 512 H = 64 9.07 -> 9.76, N = 1024 H = 32
+  //   13.5 -> 13.0; causal N = 512 H = 64 10.3 -> 10.5, N = 1000 H = 32
+  //   15.3 -> 13.8;
+  //   two groups, d = 128: N = 1024 H = 16 17.5 -> 17.8, N = 2048 H = 8
+  //   29.2 -> 27.0; causal N = 512 H = 32 13.3 -> 13.7, N = 1000 H = 16
+  //   19.6 -> 18.0 (one line for both masks all the same: up to there a
+  //   128-wide head gives the bytes of a 192-wide one, which is never split,
+  //   whose further columns are zero, and the MLA tests compare the two).
+  if ((a.d == 64 || a.dtype == 2) && a.N >= 384 && fits(64)) return 4;
+  if (a.N >= (a.d == 64 ? 768 : 1536) && fits(128)) return 2;
+  return 1;
+}
+
+// Eight waves keep K/V tiles in LDS for the most rows; four let one workgroup's
+// prologue and epilogue run beside another's key loop, which wins where
+// workgroups are short, and where the 256-row tiles, dealt out in rounds over
+// the CUs, would leave too many of them idle.
+inline int choose_waves(const AttnArgs& a, int cus) {
+  const auto tiles = [&](int rows) {
+    const long long nq = (a.N + rows - 1) / rows;
+    return (a.causal ? (nq + 1) / 2 : nq) * a.B * a.H;
+  };
+  const long long rounds8 = (tiles(256) + cus - 1) / cus, rounds4 = (tiles(128) + cus - 1) / cus;
+  // 192-wide keys run one workgroup of either size per CU: four waves where all
+  // of theirs run at once (H = 16 N = 4096 causal 104.8 -> 85.6 us; in two
+  // rounds, H = 8 N = 8192 unmasked, 270 -> 300).  Short causal pairs gain
+  // nothing (H = 128 N = 512 23.5 -> 23.9), single query blocks do.
+  if (a.d == 192) {
+    const long long blocks = (long long)((a.N + 127) / 128) * a.B * a.H;
+    return blocks <= cus || (a.N >= 768 && rounds4 == 1) ? 4 : 8;
+  }
+  // Short sequences, us, 256 -> 128 rows at a full grid: d = 128 bf16 N = 1024
+  // 133 -> 131, N = 2048 233 -> 238, causal 145 -> 142, N = 4096 440 -> 457 and
+  // 247 -> 247; d = 64 N = 2048 146 -> 138, N = 4096 274 -> 267, causal
+  // 156 -> 150; FP8 N = 4096 282 -> 280, causal 165 -> 161.
+  if (a.N <= (a.d == 64 || a.dtype == 2 ? 4096 : a.causal ? 2048 : 1024)) return 4;
+  // Longer ones: a 256-row tile takes its CU 20 units of time, two 128-row
+  // tiles side by side 21, a 128-row tile that has a CU to itself 14.  (B=3 H=32
+  // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
+  // 192 tiles of 256 rows fill 192 CUs: 104 us with them, 109 with 384 halves.)
+  return rounds4 / 2 * 21 + rounds4 % 2 * 14 < rounds8 * 20 ? 4 : 8;
+}
+
+}  // namespace qm

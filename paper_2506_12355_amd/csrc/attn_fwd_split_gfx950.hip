@@ -57,35 +57,6 @@ hipError_t launch_groups(const AttnArgs& a, const Device& dev, int groups, hipSt
 
 }  // namespace
 
-int key_groups(const AttnArgs& a, int cus) {
-  if (a.d == 192) return 1;
-  // Workgroups of query blocks of `rows` rows, causal ones in pairs where they
-  // are too many to stay single (which pays from N = 4096 on).
-  const auto fits = [&](int rows) {
-    const long long nq = (a.N + rows - 1) / rows;
-    const long long heads = (long long)a.B * a.H;
-    return nq * heads <= cus || (a.causal && a.N >= 4096 && (nq + 1) / 2 * heads <= cus);
-  };
-  // All query blocks in one round of one workgroup per CU: in two rounds the
-  // split loses to two unsplit workgroups per CU (0.6-0.9x).  Below these
-  // lengths the merge (about 1 us) outweighs the steps saved; each line lies
-  // between the sizes named (us, unsplit -> split, B = 1, unmasked unless
-  // causal is said):
-  //   four groups: d = 64 N = 256 H = 8 6.05 -> 6.57, N = 512 8.31 -> 7.93;
-  //   FP8 N = 256 7.05 -> 7.67, N = 512 9.20 -> 8.91;
-  //   two groups, d = 64: N = 512 H = 64 9.07 -> 9.76, N = 1024 H = 32
-  //   13.5 -> 13.0; causal N = 512 H = 64 10.3 -> 10.5, N = 1000 H = 32
-  //   15.3 -> 13.8;
-  //   two groups, d = 128: N = 1024 H = 16 17.5 -> 17.8, N = 2048 H = 8
-  //   29.2 -> 27.0; causal N = 512 H = 32 13.3 -> 13.7, N = 1000 H = 16
-  //   19.6 -> 18.0 (one line for both masks all the same: up to there a
-  //   128-wide head gives the bytes of a 192-wide one, which is never split,
-  //   whose further columns are zero, and the MLA tests compare the two).
-  if ((a.d == 64 || a.dtype == 2) && a.N >= 384 && fits(64)) return 4;
-  if (a.N >= (a.d == 64 ? 768 : 1536) && fits(128)) return 2;
-  return 1;
-}
-
 hipError_t launch_attn_fwd_split(const AttnArgs& a, int groups, hipStream_t stream) {
   Device dev;
   const hipError_t e = current_device(&dev);
