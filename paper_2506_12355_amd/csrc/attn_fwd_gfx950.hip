@@ -1,7 +1,8 @@
 // The instances of the attention kernel (attn_fwd_kernel.h), of which a call runs
-// the one that attn_fwd_rules.h gives: eight wavefronts (256 query rows, one workgroup per CU) or four
-// (128 rows, two or three workgroups per CU); the smallest grids and the 128-row
-// instances for other tensors are in files of their own.
+// the one that attn_fwd_rules.h gives: eight wavefronts (256 query rows, one
+// workgroup per CU) or four (128 rows, two or three workgroups per CU); the
+// smallest grids and the 128-row instances for other tensors are in files of
+// their own.
 
 #include <hip/hip_runtime.h>
 
@@ -14,9 +15,12 @@ namespace {
 
 template <int DK, int DV, int DT, bool CAUSAL, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, (wgs_per_cu<DK, WAVES>())) void attn_fwd_kernel(KParams p) {
-  // the two-block-ring instances (192-wide keys, and four waves) take
-  // [B][heads][N][w] only: runtime strides there spill registers
-  constexpr int layouts = ring_depth<DK, DV, DT, WAVES>() == 4 ? kEitherLayout : kBhndOnly;
+  // Either layout for eight waves with four-block rings only: runtime strides spill
+  // vector registers with two-block rings, and scalar ones in the four-wave FP8
+  // instance (145 against 71 unmasked), whose key loop is bound by issue: N = 2048
+  // H = 120 146.7 -> 144.0 us, H = 256 N = 2017 318 -> 305 unmasked; causal about 1%.
+  constexpr int layouts =
+      WAVES == 8 && ring_depth<DK, DV, DT, WAVES>() == 4 ? kEitherLayout : kBhndOnly;
   attn_fwd_body<DK, DV, DT, CAUSAL, WAVES, 1, layouts>(p);
 }
 

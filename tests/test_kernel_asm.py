@@ -116,6 +116,15 @@ def test_no_spills_or_scratch(asm):
     assert len(scratch) == N_INSTANCES and max(scratch) == 0
 
 
+def test_four_wave_fp8_keeps_its_scalars(asm):
+    """The unmasked four-wave FP8 instance is bound by issue: it takes contiguous heads
+    only, as with runtime row strides twice its scalar registers spill (145 against
+    71), each reload an instruction of the key loop's."""
+    name, = [n for n in _kernels(asm) if "ELi2ELb0ELi4EEEv" in n]
+    block = re.search(rf"\.name:\s+{name}\n(?:.*\n)*?\s+\.sgpr_spill_count:\s+(\d+)", asm)
+    assert int(block.group(1)) < 110
+
+
 def test_checker_sees_a_planted_hazard():
     """The hazard scan itself: a VALU write of a descriptor SGPR two instructions
     before a direct load is reported; five wait states in between clear it."""
