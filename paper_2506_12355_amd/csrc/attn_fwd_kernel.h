@@ -77,11 +77,10 @@
 // Dispatch order: workgroup i runs on XCD i % 8.  The linear tile id is
 // remapped so that consecutive query blocks of the same head (and the heads
 // sharing one key/value head) land on the same XCD and share its L2 for the
-// K/V stream.  The workgroups are persistent: as many as the CUs hold at once
-// (a multiple of 8), workgroup w taking tiles w, w + grid, ..., which keeps
-// tile t on XCD t % 8 and the same tiles side by side as one workgroup per
-// tile would.  (FP8, which launched one per tile, B=2 H=32 N=8192 causal:
-// 566 -> 548 us, H=16 B=4 N=4096 causal 160 -> 154, shorter and unmasked 0-1%.)
+// K/V stream.  The workgroups are persistent (but see tile_grid): as many as
+// the CUs hold at once (a multiple of 8), workgroup w taking tiles w, w + grid,
+// ..., which keeps tile t on XCD t % 8 and the same tiles side by side as one
+// workgroup per tile would.
 //
 // Shapes: head dimension 64 or 128 (q, k, v alike), or 192-wide queries and
 // keys with 128-wide values (the MLA shape); H query heads may share Hkv
@@ -98,6 +97,7 @@
 #include <type_traits>
 
 #include "attn_fwd_launch.h"
+#include "attn_fwd_rules.h"
 #include "tile_order.h"
 
 namespace qm {
@@ -1326,7 +1326,7 @@ hipError_t launch_tiles(const AttnArgs& a, const Device& dev, int bm, int thread
   // dispatcher deals workgroup w to XCD w % 8)
   const int resident = dev.cus * per_cu / kXcds * kXcds;
   const KParams kp = make_params(a, bm, dev.cus, resident);
-  const int grid = resident >= kXcds && resident < kp.total ? resident : kp.total;
+  const int grid = tile_grid(kp.total, resident, dev.cus, per_cu, threads, a.dtype, a.N);
   hipLaunchKernelGGL(KERN, dim3(grid), dim3(threads), lds, stream, kp);
   return hipGetLastError();
 }

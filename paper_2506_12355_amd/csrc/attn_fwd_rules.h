@@ -2,6 +2,8 @@
 // and the device's CU count: host code only.
 #pragma once
 
+#include <limits.h>
+
 #include "attn_fwd_launch.h"
 
 namespace qm {
@@ -66,6 +68,27 @@ inline int choose_waves(const AttnArgs& a, int cus) {
   // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
   // 192 tiles of 256 rows fill 192 CUs: 104 us with them, 109 with 384 halves.)
   return rounds4 / 2 * 21 + rounds4 % 2 * 14 < rounds8 * 20 ? 4 : 8;
+}
+
+// Workgroups of a launch over `total` tiles: as many as are `resident` at once, each
+// walking tiles in turn (rounds of `resident` tiles), or one per tile.
+//
+// Persistent workgroups save their set-up, but a CU keeps the tiles it was dealt.  With
+// one workgroup per tile the CU that is free first takes the next, which evens out what
+// two FP8 workgroups side by side make of their shares; only where the last round has at
+// most one tile to a CU, that gives some CUs two of them and others none.  us, persistent
+// -> one per tile, two per CU: last round above one per CU, N = 4096 H = 104 unmasked
+// 468 -> 447, N = 2048 H = 120 144.0 -> 139.7, causal N = 3582 H = 136 268.9 -> 256.9;
+// at most one, N = 4096 H = 64 unmasked 274 -> 272 but causal N = 1536 H = 211
+// 87.5 -> 92.4, N = 2560 H = 112 119.9 -> 124.9.  Short tiles are bound by their set-up
+// (N = 256 H = 496 20.8 -> 22.8), and one workgroup per CU gains 2-3% from staying.
+inline int tile_grid(int total, int resident, int cus, int per_cu, int threads, int dtype, int N) {
+  if (resident < kXcds || total <= resident) return total;
+  const int last = total % resident;
+  if (dtype == 2 && per_cu > 1 && N > 1000 && (last == 0 || last > cus) &&
+      total <= INT_MAX / threads)   // as many as a grid takes
+    return total;
+  return resident;
 }
 
 }  // namespace qm

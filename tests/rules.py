@@ -23,6 +23,9 @@ extern "C" int groups(int dtype, int B, int H, int N, int d, int causal, int cus
 extern "C" int waves(int dtype, int B, int H, int N, int d, int causal, int cus) {
   return qm::choose_waves(args(dtype, B, H, N, d, causal), cus);
 }
+extern "C" int grid(int total, int resident, int cus, int per_cu, int threads, int dtype, int N) {
+  return qm::tile_grid(total, resident, cus, per_cu, threads, dtype, N);
+}
 """
 DTYPES = {"f16": 0, "bf16": 1, "e4m3": 2}
 _lib = None

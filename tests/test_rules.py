@@ -31,3 +31,17 @@ def test_key_groups(dtype, H, N, d, causal, groups):
 ])
 def test_waves(dtype, H, N, d, causal, waves):
     assert rules.waves(dtype, 1, H, N, d, causal) == waves
+
+
+def test_grid():
+    """One workgroup per tile for FP8 two to a CU and a last round of more than one tile
+    to a CU, as far as a grid's 2^31 threads reach; else what is resident."""
+    def grid(total, dtype="e4m3", per_cu=2, N=2048, cus=256):
+        return rules.library().grid(total, cus * per_cu // 8 * 8, cus, per_cu, 256, rules.DTYPES[dtype], N)
+
+    most = (2 ** 31 - 1) // 256
+    assert [grid(t) for t in (1, 512, 513, 768, 769, 1024, 1025)] == [1, 512, 512, 512, 769, 1024, 512]
+    assert grid(most // 512 * 512) == most // 512 * 512 and grid(2 ** 31 - 1) == 512
+    assert grid(769, dtype="bf16") == 512 and grid(769, N=1000) == 512
+    assert grid(300, per_cu=1) == 256 and grid(511, per_cu=1) == 256
+    assert grid(5, cus=3) == 5   # too few CUs for a round of the XCDs
