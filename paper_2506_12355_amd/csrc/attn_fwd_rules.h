@@ -49,14 +49,13 @@ inline int choose_waves(const AttnArgs& a, int cus) {
     const long long nq = (a.N + rows - 1) / rows;
     return (a.causal ? (nq + 1) / 2 : nq) * a.B * a.H;
   };
-  const long long rounds8 = (tiles(256) + cus - 1) / cus, rounds4 = (tiles(128) + cus - 1) / cus;
   // 192-wide keys run one workgroup of either size per CU: four waves where all
   // of theirs run at once (H = 16 N = 4096 causal 104.8 -> 85.6 us; in two
   // rounds, H = 8 N = 8192 unmasked, 270 -> 300).  Short causal pairs gain
   // nothing (H = 128 N = 512 23.5 -> 23.9), single query blocks do.
   if (a.d == 192) {
     const long long blocks = (long long)((a.N + 127) / 128) * a.B * a.H;
-    return blocks <= cus || (a.N >= 768 && rounds4 == 1) ? 4 : 8;
+    return blocks <= cus || (a.N >= 768 && tiles(128) <= cus) ? 4 : 8;
   }
   // Short sequences, us, 256 -> 128 rows at a full grid: d = 128 bf16 N = 1024
   // 133 -> 131, N = 2048 233 -> 238, causal 145 -> 142, N = 4096 440 -> 457 and
@@ -67,7 +66,25 @@ inline int choose_waves(const AttnArgs& a, int cus) {
   // tiles side by side 21, a 128-row tile that has a CU to itself 14.  (B=3 H=32
   // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
   // 192 tiles of 256 rows fill 192 CUs: 104 us with them, 109 with 384 halves.)
-  return rounds4 / 2 * 21 + rounds4 % 2 * 14 < rounds8 * 20 ? 4 : 8;
+  // (Measured at d = 128; at d = 64 and with FP8 the ratio of the two sizes is within
+  // 0.97-1.10 of these costs' over 900 shapes beyond N = 4096.)
+  // An odd number of causal query blocks leaves each head's middle one without a
+  // partner, half a tile.  Where the tiles past the last whole round are such ones only
+  // (the last of an XCD's whole heads), that round takes half as long.  H = 8 N = 8256,
+  // 264 tiles of 128 rows: 256 -> 128 rows, d = 128 163.8 -> 142.8 us, d = 64
+  // 118.6 -> 93.7, FP8 126.4 -> 87.8; H = 24 N = 5376, 264 tiles of 256 rows: FP8
+  // 140.1 -> 97.2.  After a round of two 128-row tiles beside one another that holds at
+  // d = 64 only, where a third fits beside them: H = 8 N = 16500, 264 and 520 tiles,
+  // d = 64 311 -> 299, but d = 128 502 -> 530, FP8 296 -> 311.
+  const auto half_units = [&](int rows, int alone, int beside) {   // beside: two on a CU
+    const long long n = tiles(rows), left = n % cus, full = n / cus;
+    const bool singles = a.causal && (a.N + rows - 1) / rows % 2 &&
+                         (long long)a.B * a.H % kXcds == 0 && left <= kXcds &&
+                         (rows == 256 || full % 2 || a.d == 64);
+    const long long last = left == 0 ? 0 : full % 2 ? beside - alone : alone;
+    return 2 * (full / 2 * beside + full % 2 * alone) + (singles ? last : 2 * last);
+  };
+  return half_units(128, 14, 21) < half_units(256, 20, 40) ? 4 : 8;
 }
 
 // Workgroups of a launch over `total` tiles: as many as are `resident` at once, each

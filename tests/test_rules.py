@@ -28,6 +28,10 @@ def test_key_groups(dtype, H, N, d, causal, groups):
     ("bf16", 64, 8192, 128, False, 8), ("bf16", 512, 512, 128, True, 4), ("f16", 128, 4096, 64, False, 4),
     ("e4m3", 64, 8192, 128, True, 8), ("bf16", 16, 4096, 192, True, 4), ("bf16", 256, 8192, 192, True, 8),
     ("bf16", 24, 4096, 128, True, 8), ("bf16", 96, 3000, 128, False, 4),
+    # past a whole round, heads' middle blocks only (else whole pairs)
+    ("bf16", 8, 8256, 128, True, 4), ("f16", 8, 8256, 64, True, 4), ("e4m3", 8, 8193, 128, True, 4),
+    ("bf16", 8, 8321, 128, True, 8), ("e4m3", 24, 5376, 128, True, 4), ("bf16", 8, 8193, 192, True, 8),
+    ("bf16", 8, 16500, 128, True, 8), ("bf16", 8, 16500, 64, True, 4), ("e4m3", 8, 16500, 128, True, 8),
 ])
 def test_waves(dtype, H, N, d, causal, waves):
     assert rules.waves(dtype, 1, H, N, d, causal) == waves
