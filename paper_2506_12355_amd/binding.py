@@ -200,7 +200,7 @@ def fwd_fp8(q, k, v, scales, causal: bool = False, scale: float | None = None, o
         raise ValueError("k and v must hold Hkv heads matching q in B, N and d")
     scale = 1.0 / d ** 0.5 if scale is None else float(scale)   # rounded to float32 by the call
     if out is None:
-        out = q.new_empty(q.shape, dtype=torch.bfloat16)
+        out = torch.empty(q.shape, dtype=torch.bfloat16, device=device)
     elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
         raise ValueError("out must be a contiguous bfloat16 tensor shaped like q")
     lse = _lse(q, lse, B, H, N)
@@ -238,7 +238,7 @@ def _lse(q, lse, B, H, N):
     """The log-sum-exp output: the caller's, checked, or a new tensor."""
     import torch
     if lse is None:
-        return q.new_empty((B, H, N), dtype=torch.float32)
+        return torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     if lse.shape != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
         raise ValueError("lse must be a contiguous float32 tensor of shape [B, H, N]")
     return lse
@@ -249,6 +249,7 @@ def _enqueue(entry, device, stream, before, after) -> None:
     current, on `stream` (a torch stream; None: the device's current one)."""
     import torch
     index = device.index
+    # the current stream's handle alone, without a torch.cuda.Stream object around it
     raw = torch._C._cuda_getCurrentRawStream(index) if stream is None else stream.cuda_stream
     if index == torch.cuda.current_device():
         status = entry(*before, raw, *after)
@@ -312,7 +313,7 @@ def fwd(q, k, v, causal: bool = False, scale: float | None = None, out=None, lse
     # the C float argument rounds the scale to float32
     scale = 1.0 / d ** 0.5 if scale is None else float(scale)
     if out is None:
-        out = q.new_empty(qs[:3] + (dv,))
+        out = torch.empty((*qs[:3], dv), dtype=q.dtype, device=device)
     else:
         oshape = (*qs[:3], dv)
         if tuple(out.shape) != oshape or out.dtype != q.dtype or not out.is_contiguous():

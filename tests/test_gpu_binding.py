@@ -111,3 +111,18 @@ def test_outputs_and_stream_are_honoured(qa, qkv):
     assert torch.equal(o.view(torch.int16), ref_o.view(torch.int16))
     assert torch.equal(lse.view(torch.int32), ref_l.view(torch.int32))
     assert np.isfinite(lse.cpu().numpy()).all()
+
+
+def test_new_outputs_are_plain_tensors(qa, qkv):
+    """Outputs made by the call are plain tensors also for inputs of a subclass."""
+    import torch
+
+    class Tagged(torch.Tensor):
+        pass
+
+    tagged = [t.as_subclass(Tagged) for t in qkv]
+    q8 = [torch.zeros((1, 2, 40, 128), dtype=torch.uint8, device="cuda").as_subclass(Tagged)] * 3
+    for res in (qa.fwd(*tagged), qa.fwd_fp8(*q8, (1.0, 1.0, 1.0))):
+        assert [type(t) for t in res] == [torch.Tensor, torch.Tensor]
+    o, lse = qa.fwd(*qkv)
+    assert torch.equal(qa.fwd(*tagged)[0], o) and torch.equal(qa.fwd(*tagged)[1], lse)
