@@ -10,7 +10,8 @@ Extra barriers only remove overlap between waves; if the release protocol
 let a wave read a slot before its loads had landed, or load into a slot
 another wave still read, the two builds would disagree.  Covered: the bench
 workload (both masks), FP8, d = 64 in both workgroup sizes, ragged lengths,
-grouped heads, the MLA shape and [B][N][H][d].
+grouped heads, the MLA shape and [B][N][H][d]; the key groups of small 16-bit
+grids are in test_gpu_small_grids.py, those of FP8 here.
 """
 from __future__ import annotations
 
@@ -20,6 +21,7 @@ import numpy as np
 import pytest
 
 import seeded_inputs as si
+from tests import rules
 from tests.gpu_util import to_device
 
 pytestmark = pytest.mark.gpu
@@ -78,6 +80,13 @@ def _both(libs, what, tq, tk, tv, B, H, Hkv, N, d, dv, scale, dtype, layout=0, f
         lib.qm_attn_set_tile_rows(0)
 
 
+def _groups(dtype, B, H, N, d):
+    """Key groups of a workgroup under both masks on the device at hand."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return {rules.key_groups(dtype, B, H, N, d, c, cus) for c in (False, True)}
+
+
 @pytest.mark.parametrize("name", ["mha_b2_h32_n8192_d128_bf16", "grid_d64_n8192",
                                   "mha_b8_h16_n1024_d64_f16", "mha_b4_h32_n2048_d128_f16_causal",
                                   "gqa_b2_h64_kv8_n8192_d128_bf16_causal",
@@ -92,12 +101,14 @@ def test_16bit_workloads_match_checking_build(libs, name):
           tiles=tiles)
 
 
-@pytest.mark.parametrize("N,d,dtype", [(1000, 64, "f16"), (1000, 128, "bf16"), (4161, 64, "bf16"),
-                                       (3001, 128, "f16"), (65, 128, "bf16")])
-def test_ragged_lengths_match_checking_build(libs, N, d, dtype):
-    q, k, v = si.make_qkv(2, 3, N, d, dtype, seed=N + d)
+@pytest.mark.parametrize("H,N,d,dtype", [(18, 1000, 64, "f16"), (3, 1000, 128, "bf16"), (8, 4161, 64, "bf16"),
+                                         (6, 3001, 128, "f16"), (3, 65, 128, "bf16")])
+def test_ragged_lengths_match_checking_build(libs, H, N, d, dtype):
+    """Heads enough that the keys are not split, so that both tile sizes do run."""
+    assert _groups(dtype, 2, H, N, d) == {1}
+    q, k, v = si.make_qkv(2, H, N, d, dtype, seed=N + d)
     tq, tk, tv = (to_device(x, dtype) for x in (q, k, v))
-    _both(libs, f"N={N} d={d} {dtype}", tq, tk, tv, 2, 3, 3, N, d, d, si.default_scale(d),
+    _both(libs, f"N={N} d={d} {dtype}", tq, tk, tv, 2, H, H, N, d, d, si.default_scale(d),
           1 if dtype == "bf16" else 0, tiles=(128, 256))
 
 
@@ -118,3 +129,23 @@ def test_fp8_workloads_match_checking_build(libs, name):
     tq, tk, tv = (torch.from_numpy(x).cuda() for x in (q8, k8, v8))
     _both(libs, name, tq, tk, tv, w.B, w.H, w.kv_heads, w.N, w.d, w.d, w.scale, 2,
           fp8_scales=scales, tiles=(128, 256))
+
+
+@pytest.mark.parametrize("H,Hkv,N,groups,layout", [
+    (40, 8, 555, 1, 0),    # both tile sizes (the small workload above runs four key groups)
+    (40, 40, 1030, 1, 1),
+    (4, 2, 2500, 2, 0),    # two key groups
+    (4, 4, 2177, 2, 1),
+    (3, 1, 2000, 4, 1),    # four
+])
+def test_fp8_routes_match_checking_build(libs, H, Hkv, N, groups, layout):
+    import torch
+    assert _groups("e4m3", 2, H, N, 128) == {groups}
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    t = []
+    for heads in (H, Hkv, Hkv):
+        shape = (2, N, heads, 128) if layout else (2, heads, N, 128)
+        t.append(torch.randn(shape, generator=gen, device="cuda").to(torch.float8_e4m3fn).view(torch.uint8))
+    _both(libs, f"FP8 {H}/{Hkv}x{N} layout={layout}", *t, 2, H, Hkv, N, 128, 128, si.default_scale(128), 2,
+          layout=layout, fp8_scales=(1.0, 1.0, 1.0), tiles=(128, 256) if groups == 1 else (0,))

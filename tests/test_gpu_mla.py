@@ -6,7 +6,8 @@ Every workload is compared in full; the long ones (including the
 DeepSeek-V3-sized one: 128 heads, N = 8192, causal) first on sampled rows,
 then on every element with the oracle spread over processes.  Independently of the
 oracle: with the last 64 query/key columns zero, the result must equal the
-128-wide multi-head kernel's byte for byte (the extra k-steps add exact zeros).
+128-wide multi-head kernel's byte for byte (the extra k-steps add exact zeros),
+unless that splits its keys (small grids from N = 1536 on).
 """
 from __future__ import annotations
 
@@ -17,7 +18,7 @@ import pytest
 
 import seeded_inputs as si
 from oracle import attention_fp64, attention_rows_fp64
-from tests import oracle_pool
+from tests import oracle_pool, rules
 from tests.gpu_util import check_close, to_device, to_host64
 
 pytestmark = pytest.mark.gpu
@@ -61,10 +62,23 @@ def test_small_mla_workload_full(qa, name):
 @pytest.mark.parametrize("N", [1, 63, 65, 129, 255, 1000])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_mla_edge_lengths(qa, N, dtype):
+    """As chosen, and with 128 and 256 rows forced (three heads alone would only run
+    128): the same bytes."""
+    import torch
     q, k, v = si.make_qkv(1, 3, N, 192, dtype, seed=N + 191, dv=128)
     for causal in (False, True):
-        _say(f"case MLA edge N={N} {dtype} causal={causal}")
-        o, lse = _run(qa, q, k, v, dtype, causal, si.default_scale(192))
+        res = []
+        try:
+            for rows in (0, 128, 256):
+                _say(f"case MLA edge N={N} {dtype} causal={causal} tile_rows={rows or 'auto'}")
+                qa.set_tile_rows(rows)
+                res.append(_run(qa, q, k, v, dtype, causal, si.default_scale(192)))
+        finally:
+            qa.set_tile_rows(0)
+        o, lse = res[0]
+        for o2, lse2 in res[1:]:
+            assert torch.equal(o.view(torch.int16), o2.view(torch.int16))
+            assert torch.equal(lse.view(torch.int32), lse2.view(torch.int32))
         Or, lr = attention_fp64(q, k, v, si.default_scale(192), causal, dtype)
         check_close(to_host64(o), to_host64(lse), Or, lr, dtype, f"MLA N={N} causal={causal}")
 
@@ -107,11 +121,15 @@ def test_long_mla_workloads_sampled(qa, name, causal):
                              f"{name} causal={causal}")
 
 
-@pytest.mark.parametrize("N", [200, 1000])
+@pytest.mark.parametrize("H,N", [(3, 200), (17, 1000), (9, 2049)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-def test_zero_rope_part_equals_mha(qa, N, dtype):
+def test_zero_rope_part_equals_mha(qa, H, N, dtype):
+    """Where the 128-wide call does not split its keys over a workgroup's wavefronts
+    (192-wide keys never are); each 128-wide length has heads enough for that."""
     import torch
-    q, k, v = si.make_qkv(2, 3, N, 192, dtype, seed=N + 3, dv=128)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert all(rules.key_groups(dtype, 2, H, N, 128, c, cus) == 1 for c in (False, True))
+    q, k, v = si.make_qkv(2, H, N, 192, dtype, seed=N + 3, dv=128)
     q[..., 128:] = 0
     k[..., 128:] = 0
     scale = si.default_scale(192)

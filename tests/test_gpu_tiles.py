@@ -2,7 +2,9 @@
 four) give the same bytes: every query row takes the same arithmetic in the
 same order whichever tile holds it.  Each case runs with 128-row tiles forced,
 256-row tiles forced and the automatic choice, compares the three byte for
-byte, and checks the 128-row result against the oracle."""
+byte, and checks the 128-row result against the oracle.  The setting reaches only
+calls that do not split their keys over a workgroup's wavefronts: each case has
+enough heads for that, as the rule says for the device at hand."""
 from __future__ import annotations
 
 import math
@@ -13,6 +15,7 @@ import pytest
 
 import seeded_inputs as si
 from oracle import attention_fp64, attention_rows_fp64
+from tests import rules
 from tests.gpu_util import check_close, half_ulp, to_device, to_host64
 
 pytestmark = pytest.mark.gpu
@@ -33,6 +36,12 @@ def qa():
     qa.set_tile_rows(0)
 
 
+def _unsplit(dtype, B, H, N, d):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return all(rules.key_groups(dtype, B, H, N, d, c, cus) == 1 for c in (False, True))
+
+
 def _three_ways(qa, call):
     import torch
     res = []
@@ -50,9 +59,10 @@ def _three_ways(qa, call):
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,dtype", [
     (2, 3, 3, 1, 64, "f16"), (2, 3, 3, 65, 128, "bf16"), (1, 4, 2, 300, 64, "bf16"),
-    (2, 2, 2, 1000, 128, "f16"), (1, 6, 1, 2049, 128, "bf16"), (1, 2, 2, 3000, 64, "f16"),
+    (2, 2, 2, 1000, 128, "f16"), (1, 18, 3, 2049, 128, "bf16"), (1, 12, 12, 3000, 64, "f16"),
 ])
 def test_16bit_tiles_agree(qa, B, H, Hkv, N, d, dtype):
+    assert _unsplit(dtype, B, H, N, d)
     q, k, v = si.make_qkv(B, H, N, d, dtype, seed=150 + N + d, Hkv=Hkv)
     tq, tk, tv = (to_device(x, dtype) for x in (q, k, v))
     for causal in (False, True):
@@ -63,9 +73,10 @@ def test_16bit_tiles_agree(qa, B, H, Hkv, N, d, dtype):
                     f"128-row tiles N={N} d={d} causal={causal}")
 
 
-@pytest.mark.parametrize("H,Hkv,N", [(3, 3, 333), (4, 2, 2500)])
+@pytest.mark.parametrize("H,Hkv,N", [(3, 3, 333), (8, 2, 2500)])
 def test_fp8_tiles_agree(qa, H, Hkv, N):
     import torch
+    assert _unsplit("e4m3", 2, H, N, 128)
     q8, k8, v8 = si.make_qkv_fp8_dyadic(2, H, N, 128, seed=160 + N, v_binade=True, Hkv=Hkv)
     codes = [torch.from_numpy(x).cuda().view(torch.float8_e4m3fn) for x in (q8, k8, v8)]
     scales = (0.5, 2.0, 0.0123)
@@ -113,6 +124,9 @@ def test_random_shapes_tiles_agree(qa, c):
     """Seeded random shapes up to N = 5000, across the automatic choice's
     threshold: both tile sizes give the same bytes, and sampled rows match
     the oracle."""
+    c = dict(c)
+    while not _unsplit(c["dtype"], c["B"], c["H"], c["N"], c["d"]):
+        c["B"] += 1
     _say(f"case random tiles {c}")
     q, k, v = si.make_qkv(c["B"], c["H"], c["N"], c["d"], c["dtype"], seed=c["seed"],
                           Hkv=c["Hkv"])
@@ -125,3 +139,48 @@ def test_random_shapes_tiles_agree(qa, c):
     L = np.array([float(lse[b, h, i]) for b, h, i in rows])
     Or, lr = attention_rows_fp64(q, k, v, si.default_scale(c["d"]), c["causal"], c["dtype"], rows)
     check_close(O, L, Or, lr, c["dtype"], f"random tiles {c}")
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d,dtype", [
+    (2, 3, 1, 129, 64, "f16"), (1, 36, 12, 1001, 64, "bf16"), (2, 9, 9, 2049, 128, "bf16"),
+    (2, 5, 5, 255, 128, "f16"), (1, 17, 17, 4161, 64, "f16"),
+])
+def test_16bit_tiles_agree_in_bnhd(qa, B, H, Hkv, N, d, dtype):
+    """[B][N][H][d], whose 128-row instances are its own: both tile sizes give the bytes
+    of [B][H][N][d], which match the oracle."""
+    import torch
+    assert _unsplit(dtype, B, H, N, d)
+    q, k, v = si.make_qkv(B, H, N, d, dtype, seed=170 + N + d, Hkv=Hkv)
+    t = [to_device(x, dtype) for x in (q, k, v)]
+    bn = [x.transpose(1, 2).contiguous() for x in t]
+    rng = np.random.default_rng(N)
+    rows = [(B - 1, H - 1, N - 1), (0, 0, 0)] + [
+        (int(rng.integers(B)), int(rng.integers(H)), int(rng.integers(N))) for _ in range(30)]
+    ix = tuple(torch.tensor(np.array(rows).T).cuda())
+    for causal in (False, True):
+        _say(f"case bnhd tiles {B}x{H}/{Hkv}x{N}x{d} {dtype} causal={causal}")
+        o, lse = _three_ways(qa, lambda: qa.fwd(*bn, causal=causal, layout="bnhd"))
+        o = o.transpose(1, 2).contiguous()
+        o2, lse2 = qa.fwd(*t, causal=causal)
+        assert torch.equal(o.view(torch.int16), o2.view(torch.int16))
+        assert torch.equal(lse.view(torch.int32), lse2.view(torch.int32))
+        Or, lr = attention_rows_fp64(q, k, v, si.default_scale(d), causal, dtype, rows)
+        check_close(to_host64(o[ix]), to_host64(lse[ix]), Or, lr, dtype, f"bnhd tiles N={N} causal={causal}")
+
+
+@pytest.mark.parametrize("H,N", [(2, 129), (80, 555), (21, 2500), (160, 1030)])
+def test_fp8_tiles_agree_in_both_layouts(qa, H, N):
+    """FP8 likewise; 160 heads of 1030 tokens run one 128-row workgroup per tile, in more
+    than one round."""
+    import torch
+    assert _unsplit("e4m3", 1, H, N, 128)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    t = [torch.randn((1, H, N, 128), generator=gen, device="cuda").to(torch.float8_e4m3fn) for _ in range(3)]
+    bn = [x.view(torch.uint8).transpose(1, 2).contiguous() for x in t]
+    for causal in (False, True):
+        _say(f"case FP8 tiles in both layouts H={H} N={N} causal={causal}")
+        o, lse = _three_ways(qa, lambda: qa.fwd_fp8(*t, (1.0, 1.0, 1.0), causal=causal))
+        o2, lse2 = _three_ways(qa, lambda: qa.fwd_fp8(*bn, (1.0, 1.0, 1.0), causal=causal, layout="bnhd"))
+        assert torch.equal(o.view(torch.int16), o2.transpose(1, 2).contiguous().view(torch.int16))
+        assert torch.equal(lse.view(torch.int32), lse2.view(torch.int32))
