@@ -21,7 +21,8 @@ namespace qm {
 namespace {
 
 // Workgroups per CU: two, or three at d = 64, as for the [B][heads][N][w]
-// instances; 192-wide keys' rings (83 KB) leave room for one.
+// instances; 192-wide keys' rings (83 KB) leave room for one.  (Their registers, 245
+// or 252, are bounded as if two ran all the same: no instance takes more than 256.)
 template <int DK>
 constexpr int per_cu() {
   return DK == 64 ? 3 : DK == 128 ? 2 : 1;

@@ -10,11 +10,18 @@ namespace qm {
 
 // Key groups of a workgroup (1, 2 or 4) that a call runs with on a device of
 // `cus` CUs.  A function of the shape, type and mask alone: not of tile_rows or
-// layout, on which results do not depend.
+// layout, on which results do not depend.  (They do depend on the groups, whose
+// sums are taken apart: a sequence's bytes in a small batch and in a large one, or
+// on devices with other CU counts, differ within the rounding of the sums.)
 inline int key_groups(const AttnArgs& a, int cus) {
   if (a.d == 192) return 1;
   // Workgroups of query blocks of `rows` rows, causal ones in pairs where they
-  // are too many to stay single (which pays from N = 4096 on).
+  // are too many to stay single: from N = 4096 on (us, unsplit -> split, N = 4096
+  // H = 16 and N = 8192 H = 8: d = 128 75.9 -> 74.4, 137 -> 133; d = 64 52.2 -> 47.5,
+  // 92.1 -> 82.6; FP8 47.9 -> 46.8, 83.7 -> 80.7).  Up to N = 2048 pairs lose
+  // (d = 128 N = 1000 H = 64 24.8 -> 28.4, N = 2048 H = 24 35.9 -> 37.3, FP8
+  // 25.5 -> 29.1); between the two they would gain 0-4% (d = 128 N = 3000 H = 16
+  // 49.7 -> 47.6) to 15% (d = 64 40.5 -> 35.2).
   const auto fits = [&](int rows) {
     const long long nq = (a.N + rows - 1) / rows;
     const long long heads = (long long)a.B * a.H;
@@ -31,10 +38,8 @@ inline int key_groups(const AttnArgs& a, int cus) {
   //   13.5 -> 13.0; causal N = 512 H = 64 10.3 -> 10.5, N = 1000 H = 32
   //   15.3 -> 13.8;
   //   two groups, d = 128: N = 1024 H = 16 17.5 -> 17.8, N = 2048 H = 8
-  //   29.2 -> 27.0; causal N = 512 H = 32 13.3 -> 13.7, N = 1000 H = 16
-  //   19.6 -> 18.0 (one line for both masks all the same: up to there a
-  //   128-wide head gives the bytes of a 192-wide one, which is never split,
-  //   whose further columns are zero, and the MLA tests compare the two).
+  //   29.2 -> 27.0 (causal calls would gain a little sooner: N = 512 H = 32
+  //   13.3 -> 13.7, N = 1000 H = 16 18.6 -> 17.9, H = 32 19.7 -> 19.5).
   if ((a.d == 64 || a.dtype == 2) && a.N >= 384 && fits(64)) return 4;
   if (a.N >= (a.d == 64 ? 768 : 1536) && fits(128)) return 2;
   return 1;
@@ -66,8 +71,9 @@ inline int choose_waves(const AttnArgs& a, int cus) {
   // tiles side by side 21, a 128-row tile that has a CU to itself 14.  (B=3 H=32
   // N=3000: 392 -> 375 us, causal 257 -> 233; B=1 H=24 N=4096 causal, whose
   // 192 tiles of 256 rows fill 192 CUs: 104 us with them, 109 with 384 halves.)
-  // (Measured at d = 128; at d = 64 and with FP8 the ratio of the two sizes is within
-  // 0.97-1.10 of these costs' over 900 shapes beyond N = 4096.)
+  // (Where these costs say 1.05, two 128-row tiles for one of 256, 672 shapes beyond
+  // N = 4096 took 0.97-1.16 times as long: in the mean 1.06 at d = 128, 1.09 at d = 64,
+  // 1.03 with FP8.)
   // An odd number of causal query blocks leaves each head's middle one without a
   // partner, half a tile.  Where the tiles past the last whole round are such ones only
   // (the last of an XCD's whole heads), that round takes half as long.  H = 8 N = 8256,

@@ -8,8 +8,8 @@
 // 256-row tile gives, so a call of a few heads keeps more CUs busy for a
 // shorter time; no scratch memory and no second kernel are needed.  One
 // workgroup per CU (two waves per SIMD), as its rings fill most of the LDS: the
-// reason why 16-bit d = 128 stops at G = 2 (133 KB; G = 4 would need 267 KB) and
-// 192-wide keys have no instance (171 KB at G = 2).
+// reason why 16-bit d = 128 stops at G = 2 (133 KB; G = 4 would need 266 KB) and
+// 192-wide keys have no instance (166 KB at G = 2).
 //
 // What bounds it is latency: the chain of a query block's steps, each an LDS
 // round trip, a row of MFMAs and the softmax that depends on them.  Measured
