@@ -110,7 +110,11 @@ enum {
  *
  * Arithmetic: 16-bit products with fp32 accumulation on the matrix cores; the
  * softmax in fp32; probabilities rounded to `dtype` before the second product.
- * Results are deterministic: the same inputs give byte-identical outputs.
+ * Results are deterministic: the same inputs give byte-identical outputs on the
+ * same device.  A head's bytes may depend on how many heads the call has and on
+ * the device's CU count, within the rounding of fp32 sums: calls whose query
+ * blocks all fit the device at once may sum their keys in two or four groups
+ * (see qm_attn_set_tile_rows).
  *
  * Returns QM_OK or one of the QM_ERR_* codes above; every check except
  * QM_ERR_LAUNCH happens before anything is enqueued.
@@ -243,13 +247,14 @@ int qm_attn_fwd_fp8_layout(const void* q, const void* k, const void* v, void* o,
  *            over the device's CUs, would leave too many of them idle.
  *   rows = 128 or 256: that size.
  *
- * Calls whose query blocks all fit the device at once (a few heads, N >= 384,
- * equal head dimensions) run workgroups of 64 or 128 rows that split the keys
- * between their wavefronts, whatever this setting is.
+ * Calls whose query blocks all fit the device at once (a few heads, equal head
+ * dimensions) split the keys between the wavefronts of 64- or 128-row
+ * workgroups, whatever this setting is: into four groups from N = 384 on
+ * (d = 64 and FP8), into two from N = 768 (d = 64) or 1536 (d = 128 and FP8).
  *
- * Results do not depend on it: every query row takes the same arithmetic in
- * the same order, so outputs are byte-identical either way; only speed
- * changes.  Returns QM_OK, or QM_ERR_TILE for any other value (the setting is
+ * Results do not depend on the setting: every query row takes the same
+ * arithmetic in the same order under each, so outputs are byte-identical;
+ * only speed changes.  Returns QM_OK, or QM_ERR_TILE for any other value (the setting is
  * then unchanged).  Thread-safe; a call racing with attention calls on other
  * threads may or may not apply to them.
  */

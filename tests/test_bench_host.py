@@ -21,20 +21,17 @@ def test_more_than_one_gpu_exits_with_a_message(monkeypatch, capsys):
     assert "one GPU" in capsys.readouterr().err
 
 
-def _profiles_fresh():
-    """Whether the committed counter summaries were taken on the current kernel
-    source (after a kernel change they are stale until measured again, and
-    bench.py reports no traffic figure meanwhile)."""
-    text = open(bench.TRAFFIC_SUMMARY).read()
-    return re.search(r"kernel_source_sha256:\s*([0-9a-f]{64})", text).group(1) == \
-        bench.kernel_source_sha256()
+def _recorded(path):
+    """The kernel source hash a committed summary records, or None."""
+    m = re.search(r"kernel_source_sha256:\s*([0-9a-f]{64})", open(path).read())
+    return m and m.group(1)
 
 
 def test_traffic_is_reported_only_for_the_profiled_kernel_source(monkeypatch, tmp_path):
     text = open(bench.TRAFFIC_SUMMARY).read()
     value = float(re.search(r"traffic_bytes_per_launch:\s*([0-9.eE+]+)", text).group(1))
     recorded = re.search(r"kernel_source_sha256:\s*([0-9a-f]{64})", text).group(1)
-    if not _profiles_fresh():
+    if recorded != bench.kernel_source_sha256():   # measured before a kernel change
         assert bench.committed_traffic() is None
     # the source the counters were taken on gets their figure ...
     monkeypatch.setattr(bench, "kernel_source_sha256", lambda: recorded)
@@ -50,35 +47,33 @@ def test_traffic_is_reported_only_for_the_profiled_kernel_source(monkeypatch, tm
     assert bench.committed_traffic() is None
 
 
-def test_every_traffic_summary_gives_its_workloads_bytes():
-    """Each workload with a counter summary gets its traffic figure, at least
-    the algorithmic bytes (Q, K, V read once, O and lse written once)."""
-    if not _profiles_fresh():
-        pytest.skip("the counter summaries predate the current kernel source")
-    for wl in bench.TRAFFIC_SUMMARIES:
-        w = si.WORKLOADS[wl]
-        es = 1 if w.dtype == "e4m3" else 2
-        alg = (w.B * w.N * (w.H * w.d + w.kv_heads * (w.d + w.d_v)) * es
-               + w.B * w.H * w.N * (2 * w.d_v + 4))
-        t = bench.committed_traffic(wl)
-        assert t is not None and 0.99 * alg <= t <= 4 * alg, (wl, t, alg)
+@pytest.mark.parametrize("workload", sorted(bench.TRAFFIC_SUMMARIES))
+def test_traffic_summary_gives_its_workloads_bytes(monkeypatch, workload):
+    """A workload with a counter summary gets its traffic figure on the source that it
+    was measured on, at least the algorithmic bytes (Q, K, V read once, O and lse
+    written once)."""
+    recorded = _recorded(os.path.join(bench.PROFILES, bench.TRAFFIC_SUMMARIES[workload]))
+    monkeypatch.setattr(bench, "kernel_source_sha256", lambda: recorded)
+    w = si.WORKLOADS[workload]
+    es = 1 if w.dtype == "e4m3" else 2
+    alg = (w.B * w.N * (w.H * w.d + w.kv_heads * (w.d + w.d_v)) * es
+           + w.B * w.H * w.N * (2 * w.d_v + 4))
+    t = bench.committed_traffic(workload)
+    assert t is not None and 0.99 * alg <= t <= 4 * alg, (t, alg)
+
+
+def test_no_traffic_without_a_summary():
     assert bench.committed_traffic("mha_b1_h2_n128_d64_f16") is None
 
 
-def test_every_profile_summary_names_the_current_kernel_source():
-    """Each committed rocprofv3 summary that records a kernel source hash
-    records the current one (a kernel change needs fresh profiles)."""
-    if not _profiles_fresh():
-        pytest.skip("the profile summaries predate the current kernel source")
-    sha = bench.kernel_source_sha256()
-    prof = os.path.join(os.path.dirname(bench.TRAFFIC_SUMMARY))
-    found = 0
-    for name in sorted(os.listdir(prof)):
-        m = re.search(r"kernel_source_sha256:\s*([0-9a-f]{64})", open(os.path.join(prof, name)).read())
-        if m:
-            found += 1
-            assert m.group(1) == sha, f"{name} was measured on another kernel source"
-    assert found >= 2
+def test_profile_summaries_are_of_one_kernel_source():
+    """The committed rocprofv3 summaries that record a kernel source hash record the same
+    one: once some are measured again after a kernel change, none is left behind."""
+    recorded = {name: _recorded(os.path.join(bench.PROFILES, name)) for name in sorted(os.listdir(bench.PROFILES))}
+    recorded = {name: sha for name, sha in recorded.items() if sha}
+    assert len(recorded) >= 2 and len(set(recorded.values())) == 1, recorded
+    if bench.kernel_source_sha256() not in recorded.values():
+        pytest.skip("the summaries predate the current kernel source")
 
 
 def test_cpu_baseline_reports_the_oracle_on_host_cores():
